@@ -226,9 +226,8 @@ vne_status vne_entropy_estimate(vne_ctx *ctx, int32_t graph_id, const vne_probes
  * queries 0..q-1), so that every step is one SpMM + recurrence launch over
  * all of them.  Query q runs k_steps[q] steps on probes[q] for
  * graph_ids[q] and writes out[q]; each result is the one vne_entropy_estimate
- * gives for that query alone, up to the order of the FP64 reductions (the
- * per-graph sums add the same partials in the same order; only the first
- * level of the reduction differs).  All queries take one probe kind, one of
+ * gives for that query alone, up to the order of the FP64 reductions (per graph,
+ * over its own work blocks in a fixed order).  All queries take one probe kind, one of
  * RADEMACHER, COLORING or DENSE (HUTCHPP is not batched: VNE_ENOTSUP);
  * COLORING and DENSE probes must be HOST arrays here.  A graph id may appear
  * more than once.  The stacked copy of the matrices is cached for the exact
