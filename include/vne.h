@@ -216,7 +216,12 @@ vne_status vne_graph_release(vne_ctx *ctx, int32_t graph_id);
  * tiles, its tiles run as up to two concurrent chains, each chain's step
  * loop on a stream the context owns (VNE_CHAINS, default 2, 1 disables); the
  * context's stream waits for them, and the results are bitwise those of one
- * chain. */
+ * chain.  RADEMACHER, COLORING and DENSE estimates of a matrix small enough
+ * for a column of its Lanczos vector to fit in a CU's LDS (about 39 000 rows
+ * in FP32, 19 000 in FP64) run whole columns inside workgroups instead, where
+ * that is faster by a rule on sizes (VNE_RESIDENT: 0 never, 1 wherever the
+ * rows fit); VNE_TILE, VNE_SCHED and VNE_AUTOTUNE=0 keep the launched steps.
+ * Only the order of the FP64 sums differs. */
 vne_status vne_entropy_estimate(vne_ctx *ctx, int32_t graph_id, const vne_probes *probes,
                                 int32_t k_steps, uint32_t mode, vne_result *out);
 
@@ -234,7 +239,9 @@ vne_status vne_entropy_estimate(vne_ctx *ctx, int32_t graph_id, const vne_probes
  * id sequence (at most VNE_MAX_SETS such sets, default 4, least recently
  * used freed first); the column tile of the launch is picked on first use by
  * timing each admissible tile's whole captured step loop (VNE_AUTOTUNE=0
- * disables; VNE_AUTOTUNE_CACHE=<file> keeps the choices).  Errors: VNE_EINVAL for bad
+ * disables; VNE_AUTOTUNE_CACHE=<file> keeps the choices).  On a context with
+ * no HBM budget, the graphs that fit in LDS (see vne_entropy_estimate) run
+ * inside workgroups after the stacked steps of the others.  Errors: VNE_EINVAL for bad
  * ids, sizes or mode bits; VNE_ENOMEM when the HBM budget is exceeded. */
 vne_status vne_entropy_estimate_batch(vne_ctx *ctx, int32_t n_queries, const int32_t *graph_ids,
                                       const vne_probes *probes, const int32_t *k_steps,
@@ -525,7 +532,7 @@ vne_status vne_entropy_estimate_noalloc(vne_ctx *ctx, int32_t graph_id, const vn
 /* Diagnostics: the column tile (columns per work block of the Lanczos step
  * kernels) and the padded block width m_pad of the Lanczos run of the last
  * estimate on ctx (for Hutch++, its quadratic-form block; 0, 0 before any
- * estimate).  The tile comes from the autotuner on a plan's first use (it
+ * estimate; for columns run inside workgroups, the columns of one).  The tile comes from the autotuner on a plan's first use (it
  * times the whole step loop of every tile that divides the padded width,
  * concurrent chains included, and keeps the fastest); VNE_AUTOTUNE=0 keeps
  * the byte model's tile of plan creation, VNE_TILE forces one. */

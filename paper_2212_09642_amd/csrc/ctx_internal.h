@@ -59,6 +59,19 @@ struct Plan {
     std::vector<uint64_t> up_seeds;
     void *h_stage = nullptr;         // pinned staging of copy_out
     size_t h_stage_bytes = 0;
+    // on-chip runs of several matrices: kernel arguments and workgroup map,
+    // and what was last uploaded there
+    DevBuf res_args;
+    std::vector<char> up_res_args;
+};
+
+// A matrix in the row layout of the on-chip kernel, on the device.
+struct DevLayout {
+    int32_t waves = 0, rounds = 0, positions = 0;
+    bool unit = false;
+    double off_value = 0.0;
+    int64_t gathers = 0;
+    DevBuf slices, words, vals, spans, row_of, diag;
 };
 
 struct Graph {
@@ -77,6 +90,9 @@ struct Graph {
     double fro2 = 0.0;                       // ||A||_F^2 = tr(A^2) for symmetric A
     double trace = 0.0;
     int in_use = 0;                          // queries of a running server on this graph
+    // on-chip layouts by (waves, FP64), built on first use; null: the rows do
+    // not fit (or the device had no room)
+    std::map<std::pair<int, int>, std::unique_ptr<DevLayout>> layouts;
 };
 
 // Graphs stacked as one block-diagonal matrix: rows, entries, work blocks and
@@ -113,6 +129,8 @@ struct vne_ctx {
     std::string err;
     std::vector<std::unique_ptr<Graph>> graphs;
     std::map<std::vector<int32_t>, std::unique_ptr<GraphSet>> sets;
+    // matrices of a batch that run on chip: row ranges and result buffers only
+    std::map<std::vector<int32_t>, std::unique_ptr<GraphSet>> chip_sets;
     uint64_t tick = 0;                   // set use counter (eviction order)
     bool timing = false;
     int64_t t_launches = 0;
@@ -131,6 +149,9 @@ struct vne_ctx {
     // fork / join events, created on first use
     std::vector<hipStream_t> chain_streams;
     std::vector<hipEvent_t> chain_events;
+    // on-chip workgroup classes of a batch: their streams and events
+    std::vector<hipStream_t> side_streams;
+    std::vector<hipEvent_t> side_events;
     // serialises the registry (register, release, estimates) against the
     // worker thread of a server running on this context
     std::recursive_mutex mu;
@@ -219,6 +240,25 @@ vne_status collect_timing(vne_ctx *c);
 vne_status hutchpp_run(vne_ctx *c, GraphSet *set, int nr, int nh, int g_col0, int k, uint64_t seed, bool fp64,
                        bool desing, Plan **sk_out, Plan **q_out, const void *q_src = nullptr, int q_ld = 0);
 vne_status check_mode(vne_ctx *c, uint32_t mode);
+void free_plan(vne_ctx *c, Plan *p);
+void free_set(vne_ctx *c, GraphSet *s);
+vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne_result *out, Plan *extra);
+
+// On-chip runs (resident_run.hip): whole Lanczos loops inside workgroups.
+// The layout of one graph's on-chip run and its columns per workgroup, or
+// null where the launched steps are to run.
+DevLayout *chip_choice(vne_ctx *c, GraphSet *set, const Plan *p, int *cols);
+// run_lanczos on the chip for one graph (probe block to psi)
+vne_status run_chip(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, bool desing, const DevLayout *L, int cols);
+// One query per graph id: the graphs that fit on the chip in workgroups of
+// their own, beside the stacked launches of the others.
+vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_probes *pr, const int32_t *k_steps,
+                         bool fp64, bool desing, vne_result *out);
+vne_status estimate_set(vne_ctx *c, GraphSet *set, const vne_probes *pr, const int32_t *k_steps, bool fp64,
+                        bool desing, vne_result *out);
+// kinds, widths and step counts of one query per graph; the largest of each
+vne_status check_queries(vne_ctx *c, int G, const vne_probes *pr, const int32_t *k_steps, int *m_max, int *k_max);
+double step_bytes(const GraphSet *set, const Plan *p);
 
 }  // namespace rt
 }  // namespace vne

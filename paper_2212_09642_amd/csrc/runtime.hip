@@ -101,7 +101,7 @@ void free_plan(vne_ctx *c, Plan *p) {
                      &p->estimate, &p->flags, &p->partials, &p->level2, &p->probe_part, &p->seg_acc,
                      &p->long_part, &p->colors, &p->dense, &p->graph_k, &p->graph_m, &p->seeds,
                      &p->S, &p->B, &p->gram_part, &p->gram, &p->rinv, &p->rot, &p->col_tol, &p->col_stop,
-                     &p->bound_lo, &p->bound_hi, &p->adapt_args, &p->remaining};
+                     &p->bound_lo, &p->bound_hi, &p->adapt_args, &p->remaining, &p->res_args};
     for (DevBuf *b : all) dev_free(c, b);
 }
 
@@ -118,6 +118,12 @@ void free_set(vne_ctx *c, GraphSet *s) {
 void free_graph(vne_ctx *c, Graph *g) {
     dev_free(c, &g->row_ptr);
     dev_free(c, &g->col);
+    for (auto &kv : g->layouts) {
+        if (!kv.second) continue;
+        DevLayout *L = kv.second.get();
+        for (DevBuf *b : {&L->slices, &L->words, &L->vals, &L->spans, &L->row_of, &L->diag}) dev_free(c, b);
+    }
+    g->layouts.clear();
     g->alive = false;
 }
 
@@ -390,6 +396,15 @@ vne_status collect_timing(vne_ctx *c) {
     return VNE_OK;
 }
 
+// algorithmic bytes of one step launch: CSR once, v_j gathered once, v_{j-1}
+// read once, P_{j+1} written once (real columns only)
+double step_bytes(const GraphSet *set, const Plan *p) {
+    const size_t es = p->fp64 ? 8 : 4;
+    int64_t m_sum = 0;
+    for (int q = 0; q < p->G; ++q) m_sum += (int64_t)p->h_graph_m[q] * (set->h_row_begin[q + 1] - set->h_row_begin[q]);
+    return 4.0 * (set->n + 1) + (double)set->nnz * (4.0 + es) + 3.0 * (double)m_sum * es;
+}
+
 // Probe block, Lanczos steps, quadrature (declared with RunOpts).
 vne_status run_lanczos(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, bool desing,
                        const RunOpts &opt) {
@@ -451,11 +466,7 @@ vne_status run_lanczos(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, 
 
     const size_t es = p->fp64 ? 8 : 4;
     const size_t blk_elems = (size_t)set->n * p->m_pad;
-    // algorithmic bytes of one step launch: CSR once, v_j gathered once,
-    // v_{j-1} read once, P_{j+1} written once (real columns only)
-    int64_t m_sum = 0;
-    for (int q = 0; q < p->G; ++q) m_sum += (int64_t)p->h_graph_m[q] * (set->h_row_begin[q + 1] - set->h_row_begin[q]);
-    const double bytes = 4.0 * (set->n + 1) + (double)set->nnz * (4.0 + es) + 3.0 * (double)m_sum * es;
+    const double bytes = step_bytes(set, p);
     StepArgs a{};
     a.row_ptr = set->d_row_ptr;
     a.col = set->d_col;
@@ -1090,22 +1101,28 @@ vne_status make_probe_spec(vne_ctx *c, GraphSet *set, Plan *p, const vne_probes 
     return VNE_OK;
 }
 
-// One query per graph of the set, all graphs in one stacked launch per step.
+vne_status check_queries(vne_ctx *c, int G, const vne_probes *pr, const int32_t *k_steps, int *m_max, int *k_max) {
+    *m_max = *k_max = 0;
+    for (int q = 0; q < G; ++q) {
+        if (pr[q].kind != pr[0].kind) return fail(c, VNE_ENOTSUP, "a batch takes one probe kind");
+        if (pr[q].m < 1) return fail(c, VNE_EINVAL, "probe count m must be >= 1");
+        if (k_steps[q] < 1 || k_steps[q] > kMaxSteps) return fail(c, VNE_EINVAL, "k_steps must be in [1, 128]");
+        *k_max = std::max(*k_max, (int)k_steps[q]);
+        *m_max = std::max(*m_max, (int)pr[q].m);
+    }
+    if (*m_max > (1 << 20)) return fail(c, VNE_ENOTSUP, "probe count too large");
+    return VNE_OK;
+}
+
+// One query per graph of the set, all graphs in one stacked launch per step
+// (one graph that fits there: on the chip).
 vne_status estimate_set(vne_ctx *c, GraphSet *set, const vne_probes *pr, const int32_t *k_steps, bool fp64,
                         bool desing, vne_result *out) {
     const int G = set->G;
-    const int kind = pr[0].kind;
     int k_max = 0, m_max = 0;
+    VNE_TRY(check_queries(c, G, pr, k_steps, &m_max, &k_max));
     std::vector<int32_t> ms(G);
-    for (int q = 0; q < G; ++q) {
-        if (pr[q].kind != kind) return fail(c, VNE_ENOTSUP, "a batch takes one probe kind");
-        if (pr[q].m < 1) return fail(c, VNE_EINVAL, "probe count m must be >= 1");
-        if (k_steps[q] < 1 || k_steps[q] > kMaxSteps) return fail(c, VNE_EINVAL, "k_steps must be in [1, 128]");
-        k_max = std::max(k_max, (int)k_steps[q]);
-        m_max = std::max(m_max, (int)pr[q].m);
-        ms[q] = pr[q].m;
-    }
-    if (m_max > (1 << 20)) return fail(c, VNE_ENOTSUP, "probe count too large");
+    for (int q = 0; q < G; ++q) ms[q] = pr[q].m;
     Plan *p = nullptr;
     VNE_TRY(get_plan(c, set, m_max, k_max, fp64, false, 0, &p));
     p->h_graph_k.assign(k_steps, k_steps + G);
@@ -1113,8 +1130,13 @@ vne_status estimate_set(vne_ctx *c, GraphSet *set, const vne_probes *pr, const i
     ProbeSpec ps;
     int combine_kind = 0;
     VNE_TRY(make_probe_spec(c, set, p, pr, m_max, fp64, &ps, &combine_kind));
-    VNE_TRY(autotune(c, set, p, ps, desing));
-    VNE_TRY(run_lanczos(c, set, p, ps, desing));
+    int cols = 0;
+    if (const DevLayout *L = chip_choice(c, set, p, &cols)) {
+        VNE_TRY(run_chip(c, set, p, ps, desing, L, cols));
+    } else {
+        VNE_TRY(autotune(c, set, p, ps, desing));
+        VNE_TRY(run_lanczos(c, set, p, ps, desing));
+    }
     HIP_TRY(c, launch_combine_graphs((const double *)p->psi.p, p->m_pad, (const int32_t *)p->graph_m.p, G,
                                      combine_kind, (double *)p->estimate.p, c->stream));
     return copy_out(c, p, ms.data(), k_steps, out, nullptr);
@@ -1193,10 +1215,14 @@ extern "C" void vne_ctx_destroy(vne_ctx *c) {
     (void)hipStreamSynchronize(c->stream);
     for (auto &kv : c->sets) free_set(c, kv.second.get());
     c->sets.clear();
+    for (auto &kv : c->chip_sets) free_set(c, kv.second.get());
+    c->chip_sets.clear();
     for (auto &g : c->graphs)
         if (g) free_graph(c, g.get());
     for (hipStream_t cs : c->chain_streams) (void)hipStreamDestroy(cs);
     for (hipEvent_t e : c->chain_events) (void)hipEventDestroy(e);
+    for (hipStream_t cs : c->side_streams) (void)hipStreamDestroy(cs);
+    for (hipEvent_t e : c->side_events) (void)hipEventDestroy(e);
     if (c->own_stream) (void)hipStreamDestroy(c->own_stream);
     delete c;
 }
@@ -1320,14 +1346,15 @@ extern "C" vne_status vne_graph_release(vne_ctx *c, int32_t gid) {
     if (g->in_use > 0) return fail(c, VNE_EBUSY, "graph has queries in a running server");
     HIP_TRY(c, hipSetDevice(c->device));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    for (auto it = c->sets.begin(); it != c->sets.end();) {
-        if (std::find(it->first.begin(), it->first.end(), gid) != it->first.end()) {
-            free_set(c, it->second.get());
-            it = c->sets.erase(it);
-        } else {
-            ++it;
+    for (auto *sets : {&c->sets, &c->chip_sets})
+        for (auto it = sets->begin(); it != sets->end();) {
+            if (std::find(it->first.begin(), it->first.end(), gid) != it->first.end()) {
+                free_set(c, it->second.get());
+                it = sets->erase(it);
+            } else {
+                ++it;
+            }
         }
-    }
     free_graph(c, g);
     return VNE_OK;
 }
@@ -1451,11 +1478,5 @@ extern "C" vne_status vne_entropy_estimate_batch(vne_ctx *c, int32_t n_queries, 
         if (!get_graph(c, ids[q])) return fail(c, VNE_EINVAL, "unknown graph id " + std::to_string(ids[q]));
         if (probes[q].kind == VNE_PROBE_HUTCHPP) return fail(c, VNE_ENOTSUP, "Hutch++ queries are not batched");
     }
-    GraphSet *set = nullptr;
-    VNE_TRY(get_set(c, ids, &set));
-    const bool fp64 = (mode & VNE_MODE_F64) != 0;
-    const bool desing = (mode & VNE_MODE_DESING) != 0;
-    if (desing && !set->zero_rowsum)
-        return fail(c, VNE_EINVAL, "VNE_MODE_DESING needs matrices whose rows sum to zero (A 1 = 0)");
-    return estimate_set(c, set, probes, k_steps, fp64, desing, out);
+    return estimate_many(c, ids, probes, k_steps, (mode & VNE_MODE_F64) != 0, (mode & VNE_MODE_DESING) != 0, out);
 }
