@@ -330,19 +330,30 @@ struct StepCore {
         }
     }
 
-    // acc += sum over entries p in [p0, p1) of val[p] * v_j[col[p], cols],
-    // in batches of UB entries whose loads are all in flight together
-    template <int UB = U>
-    __device__ __forceinline__ void gather_from(int row, int p0, int p1, double (&acc)[CPL]) const {
-        for (int p = p0; p < p1; p += UB) {
-            Idx<UB> x;
-            int jj[UB];
-            T vv[UB], pv[UB][CPL], qv[UB][CPL];
-            const int cnt = min(UB, p1 - p);
-            batch_fetch<UB>(row, p, p1, x);
-            batch_spread<UB>(x, jj, vv);
-            batch_load<UB>(jj, cnt, pv, qv);
-            batch_acc<UB>(vv, cnt, pv, qv, acc);
+    // A longer row's further entries in batches of UM.  In the narrow FP32
+    // tiles a row of up to 64 entries is a long chain of batches, and the
+    // longest chain of a launch is its time: the batches are full ones, and
+    // the next one's columns and weights load behind the gathers (BA n = 2e5,
+    // us a step: 16 columns 65.8 -> 55.6, 24 91.4 -> 73.8, 32 90.1 -> 72.1).
+    // The wide tiles are bound by the gathers' bytes, and FP64 would lose a
+    // wave per SIMD to the registers (100 003 rows, 21 columns: 5% slower):
+    // half batches, loaded when needed.
+    static constexpr bool kAhead = sizeof(T) == 4 && U < 16;
+    static constexpr int UM = kAhead ? U : (U > 1 ? U / 2 : 1);
+
+    // acc += sum over entries p in [p0, p1) of val[p] * v_j[col[p], cols], in
+    // batches of UM entries whose loads are all in flight together; x: the
+    // first batch's columns and weights (kAhead)
+    __device__ __forceinline__ void gather_from(int row, int p0, int p1, Idx<UM> &x, double (&acc)[CPL]) const {
+        for (int p = p0; p < p1; p += UM) {
+            int jj[UM];
+            T vv[UM], pv[UM][CPL], qv[UM][CPL];
+            const int cnt = min(UM, p1 - p);
+            if (!kAhead) batch_fetch<UM>(row, p, p1, x);
+            batch_spread<UM>(x, jj, vv);
+            batch_load<UM>(jj, cnt, pv, qv);
+            if (kAhead && p + UM < p1) batch_fetch<UM>(row, p + UM, p1, x);
+            batch_acc<UM>(vv, cnt, pv, qv, acc);
         }
     }
 
@@ -509,11 +520,14 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int b, int tile0,
         settle(nxt, nxt_skip, t + NG);
         core.template batch_fetch<U>(nxt.row, nxt.p0, nxt.p1, ix);
         const Item nn = locate(t + 2 * NG);
+        typename Core::template Idx<Core::UM> more;
+        const bool longer = cur.p1 - cur.p0 > U;
+        if (Core::kAhead && longer) core.template batch_fetch<Core::UM>(cur.row, cur.p0 + U, cur.p1, more);
         double acc[CPL];
 #pragma unroll
         for (int k = 0; k < CPL; ++k) acc[k] = 0.0;
         core.template batch_acc<U>(vv, cnt, pv, qv, acc);
-        if (cur.p1 - cur.p0 > U) core.template gather_from<(U > 1 ? U / 2 : 1)>(cur.row, cur.p0 + U, cur.p1, acc);
+        if (longer) core.gather_from(cur.row, cur.p0 + U, cur.p1, more, acc);
         if (!cur_skip) {
             if (!cur.seg) {
                 double dvw[CPL], dww[CPL], dvv[CPL];
