@@ -250,6 +250,9 @@ vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne
 DevLayout *chip_choice(vne_ctx *c, GraphSet *set, const Plan *p, int *cols);
 // run_lanczos on the chip for one graph (probe block to psi)
 vne_status run_chip(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, bool desing, const DevLayout *L, int cols);
+// The FP64 layout of a graph for workgroups of up to 16 waves and max_rounds
+// rounds (null: does not fit, or on-chip runs are off or a budget is set)
+DevLayout *chip_layout(vne_ctx *c, int32_t gid, int max_rounds);
 // One query per graph id: the graphs that fit on the chip in workgroups of
 // their own, beside the stacked launches of the others.
 vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_probes *pr, const int32_t *k_steps,

@@ -26,6 +26,8 @@
 #include "ctx_internal.h"
 #include "internal.h"
 #include "kernels.h"
+#include "rational_chip.h"
+#include "wave_device.h"
 
 using namespace vne;
 using namespace vne::rt;
@@ -33,7 +35,7 @@ using namespace vne::rt;
 namespace {
 
 constexpr int kRThreads = 256;
-constexpr int kRBlocks = 512;          // grid of the row kernels (fixed: the reduction order)
+constexpr int kRBlocks = 512;          // largest grid of the row kernels
 constexpr int kRMaxCols = 128;
 constexpr int kRMaxBasis = 64;
 
@@ -148,16 +150,20 @@ __global__ void __launch_bounds__(kRThreads) k_r_basis_dots(int32_t n, int32_t m
     }
 }
 
-// out[r * mp + c] = sum over blocks of part[r][block][c] (fixed order), r < rows
+// out[r * mp + c] = sum over blocks of part[r][block][c] (fixed order), r <
+// rows; a wave per sum (one thread a sum was a chain of its 512 partials: 55
+// us a launch, most of a conjugate-gradient iteration)
 __global__ void __launch_bounds__(256) k_r_reduce(const double *part, int32_t nblk, int32_t mp, int32_t rows,
                                                   double *out) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
+    const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (t >= rows * mp) return;
     const int r = t / mp, c = t % mp;
     const double *p = part + (int64_t)r * nblk * mp + c;
     double s = 0.0;
-    for (int b = 0; b < nblk; ++b) s += p[(int64_t)b * mp];
-    out[t] = s;
+#pragma unroll 8
+    for (int b = lane; b < nblk; b += 64) s += p[(int64_t)b * mp];
+    s = wave_total(s);
+    if (lane == 63) out[t] = s;
 }
 
 // W -= sum_i h[i][c] v_i (i < nb)
@@ -449,6 +455,11 @@ extern "C" vne_status vne_rational_quadforms(vne_ctx *c, int32_t gid, const vne_
     const int64_t n = set->n;
     const size_t blk = (size_t)n * mp * 8;
     hipStream_t s = c->stream;
+    // no more blocks than have rows (256 / (mp / 2) rows a block)
+    const int nblk = (int)std::min<int64_t>(kRBlocks, (n * (mp / 2) + kRThreads - 1) / kRThreads);
+    // a small matrix: a workgroup per column, vectors in position order
+    const DevLayout *L = chip_layout(c, gid, kRChipRounds);
+    const size_t pos = L ? (size_t)L->positions : 0;
 
     // device memory of the call: basis, work blocks, small per-column arrays
     DevBuf dV, dU, dW, dX, dR, dP, dQ, dPart, dH, dSmall, dAl, dBe, dKe, dPsi, dHist, dNorm, dMean, dFlags, dInt, dApps,
@@ -463,14 +474,21 @@ extern "C" vne_status vne_rational_quadforms(vne_ctx *c, int32_t gid, const vne_
     auto A = [&](DevBuf *b, size_t bytes) {
         if (st == VNE_OK) st = dev_alloc(c, b, bytes);
     };
-    A(&dV, blk * kb);
-    A(&dU, blk);
-    A(&dW, blk);
-    A(&dX, blk);
-    A(&dR, blk);
-    A(&dP, blk);
-    A(&dQ, blk);
-    A(&dPart, (size_t)kRBlocks * kb * mp * 8);
+    if (L) {
+        A(&dV, (size_t)m * kb * pos * 8);
+        A(&dU, (size_t)m * pos * 8);
+        A(&dP, (size_t)m * pos * 8);         // w, in position order
+        A(&dW, blk);                         // the probe block
+    } else {
+        A(&dV, blk * kb);
+        A(&dU, blk);
+        A(&dW, blk);
+        A(&dX, blk);
+        A(&dR, blk);
+        A(&dP, blk);
+        A(&dQ, blk);
+        A(&dPart, (size_t)kRBlocks * kb * mp * 8);
+    }
     A(&dH, (size_t)mp * kb * kb * 8);
     A(&dSmall, (size_t)8 * kb * mp * 8);     // h, rr, rr0, pq, rr_new, ww, ww0, beta
     A(&dAl, (size_t)mp * kb * 8);
@@ -483,7 +501,7 @@ extern "C" vne_status vne_rational_quadforms(vne_ctx *c, int32_t gid, const vne_
     A(&dFlags, 4);
     A(&dInt, (size_t)mp * 4 * 3 + 64);      // live, iters, switched, remaining
     A(&dApps, (size_t)mp * 8 * (kb + 1));   // per column cumulative applications of A, and after each step
-    A(&dXi, (size_t)mp * 8);
+    A(&dXi, (size_t)mp * 8 * kb);
     A(&dFin, (size_t)std::max(1, n_fin) * 8);
     A(&dProbePart, (size_t)set->probe_blocks * mp * 8);
     A(&dStA, (size_t)mp * 8);
@@ -598,25 +616,61 @@ extern "C" vne_status vne_rational_quadforms(vne_ctx *c, int32_t gid, const vne_
         dev_free(c, &p.dense);
         if (lst != VNE_OK) return fin_all(lst);
     }
+    RChip ch{};
+    if (L) {
+        ch.slices = (const int32_t *)L->slices.p;
+        ch.words = (const uint32_t *)L->words.p;
+        ch.vals = (const double *)L->vals.p;
+        ch.spans = (const int32_t *)L->spans.p;
+        ch.row_of = (const int32_t *)L->row_of.p;
+        ch.diag = (const double *)L->diag.p;
+        ch.scale = set->scale;
+        ch.off_value = L->off_value;
+        ch.waves = L->waves;
+        ch.rounds = L->rounds;
+        ch.positions = L->positions;
+        ch.word_rows = (int32_t)(L->words.bytes / 256);
+        ch.unit = L->unit;
+        ch.kb = kb;
+        ch.cols = m;
+        ch.V = V;
+        ch.U = U;
+        ch.W = P;
+    }
     // v_1 = c / ||c|| (ww = ww0 = ||c||^2); columns past m are zero
-    R_TRY(hipMemcpyAsync(ww, dNorm.p, (size_t)mp * 8, hipMemcpyDeviceToDevice, s));
-    R_TRY(hipMemcpyAsync(ww0, dNorm.p, (size_t)mp * 8, hipMemcpyDeviceToDevice, s));
-    hipLaunchKernelGGL(k_r_normalize, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp, W, ww, ww0, V);
+    if (L) {
+        R_TRY(launch_rchip_start(ch, W, mp, (const double *)dNorm.p, s));
+    } else {
+        R_TRY(hipMemcpyAsync(ww, dNorm.p, (size_t)mp * 8, hipMemcpyDeviceToDevice, s));
+        R_TRY(hipMemcpyAsync(ww0, dNorm.p, (size_t)mp * 8, hipMemcpyDeviceToDevice, s));
+        hipLaunchKernelGGL(k_r_normalize, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp, W, ww, ww0, V);
+    }
     hipLaunchKernelGGL(k_r_init_ke, dim3(1), dim3(256), 0, s, (const double *)dNorm.p, m, mp, ke);
     RMat am{set->d_row_ptr, set->d_col, (const double *)set->val64.p, set->scale, (int32_t)n, mp};
     std::vector<double> h_xi(mp, 0.0);
+    if (!switching && kb > 1) {
+        std::vector<double> all((size_t)(kb - 1) * mp, 0.0);
+        for (int j = 1; j < kb; ++j)
+            for (int cc = 0; cc < m; ++cc) all[(size_t)(j - 1) * mp + cc] = std::isfinite(fin[j - 1]) ? fin[j - 1] : 0.0;
+        R_TRY(hipMemcpyAsync(dXi.p, all.data(), all.size() * 8, hipMemcpyHostToDevice, s));
+        R_TRY(hipStreamSynchronize(s));     // all leaves scope
+    }
     std::vector<int32_t> h_live(mp, 0), h_sw(mp, 0);
     bool all_switched = false;
     int64_t total_cg = 0;
     int steps_done = 0;
     for (int j = 1; j <= kb; ++j) {
-        const double *vj = V + (size_t)(j - 1) * n * mp;
         // u_j = A v_j, H(1:j, j) = V_j^T u_j
-        hipLaunchKernelGGL(k_r_apply, dim3(kRBlocks), dim3(kRThreads), 0, s, am, vj, U, (const double *)nullptr,
-                           (const int32_t *)nullptr, (double *)nullptr);
-        hipLaunchKernelGGL(k_r_basis_dots, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp, V, j, U, part);
-        hipLaunchKernelGGL(k_r_reduce, dim3((j * mp + 255) / 256), dim3(256), 0, s, part, kRBlocks, mp, j, h);
-        hipLaunchKernelGGL(k_r_store_h, dim3((j * mp + 255) / 256), dim3(256), 0, s, (const double *)h, j, mp, kb, H);
+        if (L) {
+            R_TRY(launch_rchip_project(ch, j, H, s));
+        } else {
+            const double *vj = V + (size_t)(j - 1) * n * mp;
+            hipLaunchKernelGGL(k_r_apply, dim3(nblk), dim3(kRThreads), 0, s, am, vj, U, (const double *)nullptr,
+                               (const int32_t *)nullptr, (double *)nullptr);
+            hipLaunchKernelGGL(k_r_basis_dots, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp, V, j, U, part);
+            hipLaunchKernelGGL(k_r_reduce, dim3((j * mp + 3) / 4), dim3(256), 0, s, part, nblk, mp, j, h);
+            hipLaunchKernelGGL(k_r_store_h, dim3((j * mp + 255) / 256), dim3(256), 0, s, (const double *)h, j, mp, kb, H);
+        }
         // psi_j from H_j
         hipLaunchKernelGGL(k_r_tridiag, dim3(mp), dim3(64), 0, s, H, kb, j, ke, (double *)dAl.p, (double *)dBe.p,
                            (int32_t *)dKe.p);
@@ -630,20 +684,27 @@ extern "C" vne_status vne_rational_quadforms(vne_ctx *c, int32_t gid, const vne_
         if (j == kb) break;
         // w_j orthogonalized twice against v_1..v_j (classical Gram-Schmidt),
         // with ||w||^2 before (ww0) and after (ww)
-        auto orthogonalize = [&]() {
-            hipLaunchKernelGGL(k_r_dot, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)W,
+        // (L: of u_j or w_j, committed to the basis with `last`)
+        bool committed = false;
+        auto orthogonalize = [&](bool from_u, bool last) -> hipError_t {
+            if (L) {
+                committed = last;
+                return launch_rchip_orthogonalize(ch, j, from_u, last, ww, ww0, ke, s);
+            }
+            hipLaunchKernelGGL(k_r_dot, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)W,
                                (const double *)W, part);
-            hipLaunchKernelGGL(k_r_reduce, dim3((mp + 255) / 256), dim3(256), 0, s, part, kRBlocks, mp, 1, ww0);
+            hipLaunchKernelGGL(k_r_reduce, dim3((mp + 3) / 4), dim3(256), 0, s, part, nblk, mp, 1, ww0);
             for (int pass = 0; pass < 2; ++pass) {
-                hipLaunchKernelGGL(k_r_basis_dots, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp, V, j,
+                hipLaunchKernelGGL(k_r_basis_dots, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp, V, j,
                                    (const double *)W, part);
-                hipLaunchKernelGGL(k_r_reduce, dim3((j * mp + 255) / 256), dim3(256), 0, s, part, kRBlocks, mp, j, h);
-                hipLaunchKernelGGL(k_r_basis_axpy, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp, V, j,
+                hipLaunchKernelGGL(k_r_reduce, dim3((j * mp + 3) / 4), dim3(256), 0, s, part, nblk, mp, j, h);
+                hipLaunchKernelGGL(k_r_basis_axpy, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp, V, j,
                                    (const double *)h, W);
             }
-            hipLaunchKernelGGL(k_r_dot, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)W,
+            hipLaunchKernelGGL(k_r_dot, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)W,
                                (const double *)W, part);
-            hipLaunchKernelGGL(k_r_reduce, dim3((mp + 255) / 256), dim3(256), 0, s, part, kRBlocks, mp, 1, ww);
+            hipLaunchKernelGGL(k_r_reduce, dim3((mp + 3) / 4), dim3(256), 0, s, part, nblk, mp, 1, ww);
+            return hipGetLastError();
         };
         bool w_ready = false;    // W holds the orthogonalized polynomial direction
         // the pole of step j
@@ -651,8 +712,8 @@ extern "C" vne_status vne_rational_quadforms(vne_ctx *c, int32_t gid, const vne_
             if (!all_switched) {
                 // the polynomial direction of every column first: beta_j of
                 // the bound (Theorem 4.8) that the switch rule reads
-                R_TRY(hipMemcpyAsync(W, U, blk, hipMemcpyDeviceToDevice, s));
-                orthogonalize();
+                if (!L) R_TRY(hipMemcpyAsync(W, U, blk, hipMemcpyDeviceToDevice, s));
+                R_TRY(orthogonalize(true, false));
                 w_ready = true;
                 hipLaunchKernelGGL(k_r_beta_next, dim3(1), dim3(256), 0, s, (const double *)ww, (const double *)ww0,
                                    (const int32_t *)ke, j, mp, kb, (double *)dBe.p);
@@ -669,37 +730,43 @@ extern "C" vne_status vne_rational_quadforms(vne_ctx *c, int32_t gid, const vne_
         } else {
             const double xi = fin[j - 1];
             for (int cc = 0; cc < mp; ++cc) h_xi[cc] = cc < m && std::isfinite(xi) ? xi : 0.0;
-            R_TRY(hipMemcpyAsync(dXi.p, h_xi.data(), (size_t)mp * 8, hipMemcpyHostToDevice, s));
         }
+        const double *d_xi = (const double *)dXi.p + (switching ? 0 : (size_t)(j - 1) * mp);
         // w = u_j, or the solution of (I - A / xi) w = u_j by conjugate gradients
-        bool any = false;
+        bool any = false, from_u = false;
         for (int cc = 0; cc < mp; ++cc) {
             h_live[cc] = h_xi[cc] != 0.0 ? 1 : 0;
             any = any || h_live[cc];
         }
         if (!any) {
-            if (!w_ready) R_TRY(hipMemcpyAsync(W, U, blk, hipMemcpyDeviceToDevice, s));
+            if (!w_ready) {
+                from_u = true;
+                if (!L) R_TRY(hipMemcpyAsync(W, U, blk, hipMemcpyDeviceToDevice, s));
+            }
+        } else if (L) {
+            w_ready = false;
+            R_TRY(launch_rchip_solve(ch, d_xi, tol * tol, cg_max, iters, apps, s));
         } else {
             w_ready = false;
             R_TRY(hipMemcpyAsync(live, h_live.data(), (size_t)mp * 4, hipMemcpyHostToDevice, s));
             R_TRY(hipMemsetAsync(iters, 0, (size_t)mp * 4, s));
-            hipLaunchKernelGGL(k_r_cg_init, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)U,
+            hipLaunchKernelGGL(k_r_cg_init, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)U,
                                (const int32_t *)live, W, R, P);
-            hipLaunchKernelGGL(k_r_dot, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)R,
+            hipLaunchKernelGGL(k_r_dot, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)R,
                                (const double *)R, part);
-            hipLaunchKernelGGL(k_r_reduce, dim3((mp + 255) / 256), dim3(256), 0, s, part, kRBlocks, mp, 1, rr);
+            hipLaunchKernelGGL(k_r_reduce, dim3((mp + 3) / 4), dim3(256), 0, s, part, nblk, mp, 1, rr);
             R_TRY(hipMemcpyAsync(rr0, rr, (size_t)mp * 8, hipMemcpyDeviceToDevice, s));
             for (int it = 0; it < cg_max; ++it) {
-                hipLaunchKernelGGL(k_r_apply, dim3(kRBlocks), dim3(kRThreads), 0, s, am, (const double *)P, Q,
-                                   (const double *)dXi.p, (const int32_t *)live, part);
-                hipLaunchKernelGGL(k_r_reduce, dim3((mp + 255) / 256), dim3(256), 0, s, part, kRBlocks, mp, 1, pq);
-                hipLaunchKernelGGL(k_r_cg_update, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp,
+                hipLaunchKernelGGL(k_r_apply, dim3(nblk), dim3(kRThreads), 0, s, am, (const double *)P, Q,
+                                   d_xi, (const int32_t *)live, part);
+                hipLaunchKernelGGL(k_r_reduce, dim3((mp + 3) / 4), dim3(256), 0, s, part, nblk, mp, 1, pq);
+                hipLaunchKernelGGL(k_r_cg_update, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp,
                                    (const double *)rr, (const double *)pq, (const int32_t *)live, (const double *)P,
                                    (const double *)Q, W, R, part);
-                hipLaunchKernelGGL(k_r_reduce, dim3((mp + 255) / 256), dim3(256), 0, s, part, kRBlocks, mp, 1, rrn);
+                hipLaunchKernelGGL(k_r_reduce, dim3((mp + 3) / 4), dim3(256), 0, s, part, nblk, mp, 1, rrn);
                 hipLaunchKernelGGL(k_r_cg_scalars, dim3(1), dim3(256), 0, s, mp, rr, (const double *)rrn,
                                    (const double *)rr0, tol * tol, cg_max, live, iters, apps, cgb, remaining);
-                hipLaunchKernelGGL(k_r_cg_dir, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp,
+                hipLaunchKernelGGL(k_r_cg_dir, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp,
                                    (const double *)cgb, (const int32_t *)live, (const double *)R, P);
                 if ((it & 7) == 7 || it + 1 == cg_max) {
                     int32_t rem = 0;
@@ -713,11 +780,21 @@ extern "C" vne_status vne_rational_quadforms(vne_ctx *c, int32_t gid, const vne_
             R_TRY(hipStreamSynchronize(s));
             for (int cc = 0; cc < m; ++cc) total_cg += hi[cc];
         }
-        if (!w_ready) orthogonalize();
-        hipLaunchKernelGGL(k_r_normalize, dim3(kRBlocks), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)W,
+        if (!w_ready) R_TRY(orthogonalize(from_u, true));
+        if (L) {
+            if (!committed) R_TRY(launch_rchip_commit(ch, j, (const double *)ww, (const double *)ww0, ke, s));
+            continue;
+        }
+        hipLaunchKernelGGL(k_r_normalize, dim3(nblk), dim3(kRThreads), 0, s, (int32_t)n, mp, (const double *)W,
                            (const double *)ww, (const double *)ww0, V + (size_t)j * n * mp);
         // basis size: a column grows while its new vector is not zero
         hipLaunchKernelGGL(k_r_grow, dim3(1), dim3(256), 0, s, (const double *)ww, (const double *)ww0, j, mp, ke);
+    }
+    if (L) {
+        std::vector<int32_t> hi(mp);
+        R_TRY(hipMemcpyAsync(hi.data(), iters, (size_t)mp * 4, hipMemcpyDeviceToHost, s));
+        R_TRY(hipStreamSynchronize(s));
+        for (int cc = 0; cc < m; ++cc) total_cg += hi[cc];
     }
     // results
     std::vector<double> hist((size_t)mp * kb);

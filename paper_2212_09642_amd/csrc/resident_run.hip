@@ -165,6 +165,13 @@ DevLayout *chip_choice(vne_ctx *c, GraphSet *set, const Plan *p, int *cols) {
     return slower((double)L->gathers, *cols) ? nullptr : L;
 }
 
+DevLayout *chip_layout(vne_ctx *c, int32_t gid, int max_rounds) {
+    const Graph *g = get_graph(c, gid);
+    if (chip_mode() == 0 || c->budget != 0 || g->n > (int64_t)1024 * max_rounds) return nullptr;
+    DevLayout *L = layout_of(c, gid, (int)std::min<int64_t>(16, (g->n + 63) / 64), true);
+    return L && L->rounds <= max_rounds ? L : nullptr;
+}
+
 vne_status run_chip(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, bool desing, const DevLayout *L,
                     int cols) {
     c->last_tile = cols;
