@@ -26,14 +26,17 @@
 // d that come earlier in the visiting order, and the first-fit scan marks
 // their colours in a per-colour stamp array.
 //
-// Either way the lists do not depend on the colours: worker threads list
-// them for the next chunk of the visiting order while the calling thread
-// runs the first-fit scans of the current chunk, one thread per distance.
+// Either way the lists do not depend on the colours: worker threads list the
+// balls of the coming nodes of the visiting order, in blocks, while one thread
+// per distance runs its first-fit scan behind them.  Distances whose ball is a
+// row of the matrix (a = 1: d = 1 and 2) scan the rows and need no lists.
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cstdint>
 #include <cstdlib>
+#include <functional>
 #include <memory>
-#include <numeric>
 #include <string>
 #include <thread>
 #include <vector>
@@ -57,15 +60,14 @@ int64_t bitset_cap() {
     return int64_t(256) << 20;
 }
 
-// Lists of one chunk: node t0 + j lists its nodes in
-// items[begin[j] .. begin[j + 1]) (per worker, nodes interleaved by worker),
-// by nondecreasing distance.
-struct ChunkLists {
+// Lists of a block of the visiting order: position t lists its nodes in
+// items[begin[t - t0] .. begin[t - t0 + 1]), by nondecreasing distance.
+struct BlockLists {
     int64_t t0 = 0, t1 = 0;
-    int nw = 1;
-    std::vector<std::vector<int32_t>> items;     // per worker
-    std::vector<std::vector<uint8_t>> depth;     // per worker: distance of each listed node
-    std::vector<std::vector<int64_t>> begin;     // per worker, per owned node + 1
+    std::vector<int32_t> items;
+    std::vector<uint8_t> depth;                  // distance of each listed node
+    std::vector<int64_t> begin;
+    std::atomic<int64_t> ready{-1};              // the block that is listed here
 };
 
 // one per worker thread, on cache lines of its own (the frontier vectors
@@ -115,46 +117,50 @@ private:
     std::vector<int32_t> frontier_, next_;
 };
 
-void build_lists(ChunkLists *cl, std::vector<std::unique_ptr<Searcher>> &srch, const std::vector<int32_t> &order) {
-    const int nw = cl->nw;
-    auto work = [&](int w) {
-        // fill vectors local to the thread, hand them over at the end
-        std::vector<int32_t> it;
-        std::vector<uint8_t> dp;
-        std::vector<int64_t> bg;
-        it.swap(cl->items[w]);
-        dp.swap(cl->depth[w]);
-        bg.swap(cl->begin[w]);
-        it.clear();
-        dp.clear();
-        bg.clear();
-        bg.push_back(0);
-        for (int64_t t = cl->t0 + w; t < cl->t1; t += nw) {
-            srch[w]->list(order[t], (int32_t)t, &it, &dp);
-            bg.push_back((int64_t)it.size());
-        }
-        cl->items[w].swap(it);
-        cl->depth[w].swap(dp);
-        cl->begin[w].swap(bg);
-    };
-    if (nw == 1) {
-        work(0);
-        return;
+void build_lists(BlockLists *bl, Searcher *srch, const std::vector<int32_t> &order) {
+    // (local while they grow: the vectors of neighbouring blocks share lines)
+    std::vector<int32_t> it;
+    std::vector<uint8_t> dp;
+    std::vector<int64_t> bg;
+    it.swap(bl->items);
+    dp.swap(bl->depth);
+    bg.swap(bl->begin);
+    it.clear();
+    dp.clear();
+    bg.assign(1, 0);
+    for (int64_t t = bl->t0; t < bl->t1; ++t) {
+        srch->list(order[t], (int32_t)t, &it, &dp);
+        bg.push_back((int64_t)it.size());
     }
-    std::vector<std::thread> th;
-    for (int w = 1; w < nw; ++w) th.emplace_back(work, w);
-    work(0);
-    for (auto &x : th) x.join();
+    bl->items.swap(it);
+    bl->depth.swap(dp);
+    bl->begin.swap(bg);
 }
 
-// the lists of node t of a chunk: [*q0, *q1) in the worker's arrays
-inline void node_range(const ChunkLists &cl, int64_t t, int *wk, int64_t *q0, int64_t *q1) {
-    const int64_t r = t - cl.t0;
-    *wk = (int)(r % cl.nw);
-    const int64_t slot = r / cl.nw;
-    *q0 = cl.begin[*wk][slot];
-    *q1 = cl.begin[*wk][slot + 1];
-}
+// The nodes within a distance of the node at position t: from the lists ...
+struct ListedBalls {
+    const BlockLists &bl;
+    int64_t t0() const { return bl.t0; }
+    int64_t t1() const { return bl.t1; }
+    template <class F>
+    void each(int64_t t, int32_t, int32_t dist, const F &f) const {
+        for (int64_t q = bl.begin[t - bl.t0]; q < bl.begin[t - bl.t0 + 1] && bl.depth[q] <= dist; ++q) f(bl.items[q]);
+    }
+};
+
+// ... or, for distances up to 1, the node and its row
+struct RowBalls {
+    int64_t n;
+    const int32_t *rp, *ci;
+    int64_t t0() const { return 0; }
+    int64_t t1() const { return n; }
+    template <class F>
+    void each(int64_t, int32_t i, int32_t dist, const F &f) const {
+        f(i);
+        if (dist == 0) return;
+        for (int32_t p = rp[i]; p < rp[i + 1]; ++p) f(ci[p]);
+    }
+};
 
 // First-fit state of one distance d, half-depth route: per node, the
 // colours within distance b of it among the coloured nodes, as W 64-bit words.
@@ -197,53 +203,49 @@ struct BallFit {
         return true;
     }
 
-    // WW: the word count W as a compile-time constant (0: any)
-    template <int WW>
-    void scan_w(const ChunkLists &cl, const std::vector<int32_t> &order, int64_t *t_next) {
-        const int Wn = WW > 0 ? WW : W;
-        std::vector<uint64_t> forb(Wn);
-        for (int64_t t = *t_next; t < cl.t1; ++t) {
-            int wk;
-            int64_t q0, q1;
-            node_range(cl, t, &wk, &q0, &q1);
-            const auto &it = cl.items[wk];
-            const auto &dp = cl.depth[wk];
-            // union over the distance-a ball (listed by distance)
+    // WW: the word count W as a compile-time constant
+    template <int WW, class Balls>
+    void scan_w(const Balls &balls, const std::vector<int32_t> &order, int64_t *t_next) {
+        constexpr int Wn = WW;
+        uint64_t forb[kMaxWords];
+        uint64_t *const sets = bits.data();
+        for (int64_t t = *t_next; t < balls.t1(); ++t) {
+            const int32_t i = order[t];
+            // union over the distance-a ball
             for (int w = 0; w < Wn; ++w) forb[w] = 0;
-            for (int64_t q = q0; q < q1 && dp[q] <= a; ++q) {
-                const uint64_t *src = &bits[(size_t)it[q] * Wn];
+            balls.each(t, i, a, [&](int32_t y) {
+                const uint64_t *src = sets + (size_t)y * Wn;
                 for (int w = 0; w < Wn; ++w) forb[w] |= src[w];
-            }
+            });
             int w = 0;
             while (w < Wn && forb[w] == ~0ull) ++w;
             const int32_t c = w * 64 + (w < Wn ? __builtin_ctzll(~forb[w]) : 0);
             if (c >= 64 * Wn) {
                 // every colour of the W words is taken: one more word, and
-                // the rest of the chunk with the new width
-                *t_next = widen() ? t : cl.t1;
+                // the rest with the new width
+                *t_next = widen() ? t : balls.t1();
                 return;
             }
-            const int32_t i = order[t];
             color[i] = c;
             ncol = std::max(ncol, c + 1);
             // mark c in the sets of the distance-b ball
             const uint64_t m = 1ull << (c & 63);
-            for (int64_t q = q0; q < q1 && dp[q] <= b; ++q) bits[(size_t)it[q] * Wn + w] |= m;
+            balls.each(t, i, b, [&](int32_t y) { sets[(size_t)y * Wn + w] |= m; });
         }
-        *t_next = cl.t1;
+        *t_next = balls.t1();
     }
 
     bool finished() const { return overflow; }
 
-    void scan(const ChunkLists &cl, const std::vector<int32_t> &order) {
-        int64_t t = cl.t0;
-        while (t < cl.t1 && !overflow) {
+    template <class Balls>
+    void scan(const Balls &balls, const std::vector<int32_t> &order) {
+        int64_t t = balls.t0();
+        while (t < balls.t1() && !overflow) {
             switch (W) {
-                case 1: scan_w<1>(cl, order, &t); break;
-                case 2: scan_w<2>(cl, order, &t); break;
-                case 3: scan_w<3>(cl, order, &t); break;
-                case 4: scan_w<4>(cl, order, &t); break;
-                default: scan_w<0>(cl, order, &t); break;
+                case 1: scan_w<1>(balls, order, &t); break;
+                case 2: scan_w<2>(balls, order, &t); break;
+                case 3: scan_w<3>(balls, order, &t); break;
+                default: scan_w<4>(balls, order, &t); break;
             }
         }
     }
@@ -265,14 +267,10 @@ struct DirectFit {
 
     bool finished() const { return false; }
 
-    void scan(const ChunkLists &cl, const std::vector<int32_t> &order) {
-        for (int64_t t = cl.t0; t < cl.t1; ++t) {
-            int wk;
-            int64_t q0, q1;
-            node_range(cl, t, &wk, &q0, &q1);
-            const auto &it = cl.items[wk];
-            const auto &dp = cl.depth[wk];
-            for (int64_t q = q0; q < q1 && dp[q] <= d; ++q) banned[color[it[q]]] = t;
+    template <class Balls>
+    void scan(const Balls &balls, const std::vector<int32_t> &order) {
+        for (int64_t t = balls.t0(); t < balls.t1(); ++t) {
+            balls.each(t, order[t], d, [&](int32_t y) { banned[color[y]] = t; });
             int32_t c = 0;
             while (c < ncol && banned[c] == t) ++c;
             if (c == ncol) {
@@ -288,80 +286,140 @@ int color_threads(int64_t n) {
     int nw = (int)std::thread::hardware_concurrency();
     if (const char *e = std::getenv("VNE_COLOR_THREADS")) nw = std::atoi(e);
     nw = std::max(1, std::min(nw, 16));
-    return n < 4096 ? 1 : nw;
+    // (a thread costs the time of some hundred short lists)
+    return (int)std::min<int64_t>(nw, 1 + n / 512);
 }
 
-// Lists to `depth` (whole balls, or earlier nodes when pos is given) chunk by
-// chunk, each chunk scanned by every fit of `fits` (one thread per fit)
-// while the next chunk is listed; stops early once every fit has given up.
+// Lists to `depth` (whole balls, or earlier nodes when pos is given) in
+// blocks of the visiting order; every fit of `fits` scans them in order, a
+// thread per fit, behind the threads that list.  Ends early once every fit
+// has given up.
+constexpr int64_t kBlockNodes = 64;
+constexpr int64_t kPendingNodes = int64_t(1) << 25;    // listed nodes that wait for a scan
+
 template <class Fit>
 void run_pipeline(int64_t n, const int32_t *rp, const int32_t *ci, const std::vector<int32_t> &order,
                   int32_t depth, const int32_t *pos, std::vector<Fit *> &fits) {
-    const int nw = color_threads(n);
-    std::vector<std::unique_ptr<Searcher>> srch;
-    for (int w = 0; w < nw; ++w) srch.emplace_back(new Searcher(n, rp, ci, depth, pos));
-    // chunk sizes: aim at about 2^24 listed nodes per chunk
-    const int64_t kBudget = int64_t(1) << 24;
-    int64_t chunk = std::min<int64_t>(n, 1024);
-    ChunkLists cur, nxt;
-    for (ChunkLists *cl : {&cur, &nxt}) {
-        cl->nw = nw;
-        cl->items.resize(nw);
-        cl->depth.resize(nw);
-        cl->begin.resize(nw);
+    const int nf = (int)fits.size(), nw = color_threads(n);
+    const int64_t nblk = (n + kBlockNodes - 1) / kBlockNodes;
+    auto place = [&](BlockLists *bl, int64_t k) {
+        bl->t0 = k * kBlockNodes;
+        bl->t1 = std::min<int64_t>(n, bl->t0 + kBlockNodes);
+    };
+    auto finished = [&]() {
+        for (Fit *f : fits)
+            if (!f->finished()) return false;
+        return true;
+    };
+    if (nw == 1) {
+        Searcher srch(n, rp, ci, depth, pos);
+        BlockLists bl;
+        for (int64_t k = 0; k < nblk && !finished(); ++k) {
+            place(&bl, k);
+            build_lists(&bl, &srch, order);
+            for (Fit *f : fits) f->scan(ListedBalls{bl}, order);
+        }
+        return;
     }
-    cur.t0 = 0;
-    cur.t1 = chunk;
-    build_lists(&cur, srch, order);
-    const int nf = (int)fits.size();
-    while (cur.t0 < n) {
-        // size the next chunk from this one's mean list length
-        int64_t total = 0;
-        for (int w = 0; w < nw; ++w) total += (int64_t)cur.items[w].size();
-        const double mean = std::max(1.0, (double)total / (double)std::max<int64_t>(1, cur.t1 - cur.t0));
-        chunk = std::max<int64_t>(256, std::min<int64_t>(1 << 16, (int64_t)(kBudget / mean)));
-        nxt.t0 = cur.t1;
-        nxt.t1 = std::min<int64_t>(n, cur.t1 + chunk);
-        std::thread lister;
-        if (nxt.t0 < n) lister = std::thread([&]() { build_lists(&nxt, srch, order); });
-        std::vector<std::thread> scanners;
-        for (int q = 1; q < nf; ++q) scanners.emplace_back([&, q]() { fits[q]->scan(cur, order); });
-        if (nf > 0) fits[0]->scan(cur, order);
-        for (auto &x : scanners) x.join();
-        if (lister.joinable()) lister.join();
-        std::swap(cur, nxt);
-        if (cur.t0 >= n) break;
-        bool all = true;
-        for (Fit *f : fits) all = all && f->finished();
-        if (all) break;
-    }
+    // block k is listed into ring[k mod R] once every fit is past block k - R
+    const int64_t R = 8 * nw;
+    std::vector<BlockLists> ring(R);
+    std::vector<std::atomic<int64_t>> at(nf);          // blocks that fit q is past
+    for (auto &x : at) x.store(0);
+    std::atomic<int64_t> next{0}, longest{1};          // longest: most nodes listed in a block
+    auto behind = [&]() {
+        int64_t lo = nblk;
+        for (auto &x : at) lo = std::min(lo, x.load(std::memory_order_acquire));
+        return lo;
+    };
+    auto pause = [](int *spins) {
+        if (++*spins < 256) std::this_thread::yield();
+        else std::this_thread::sleep_for(std::chrono::microseconds(20));
+    };
+    auto lister = [&]() {
+        Searcher srch(n, rp, ci, depth, pos);
+        for (int64_t k = next.fetch_add(1); k < nblk; k = next.fetch_add(1)) {
+            BlockLists &bl = ring[k % R];
+            int spins = 0;
+            while (behind() + std::min(R, std::max<int64_t>(1, kPendingNodes / longest.load())) <= k) pause(&spins);
+            if (behind() >= nblk) return;              // every fit has given up
+            place(&bl, k);
+            build_lists(&bl, &srch, order);
+            const int64_t len = (int64_t)bl.items.size();
+            for (int64_t was = longest.load(); was < len && !longest.compare_exchange_weak(was, len);) {
+            }
+            bl.ready.store(k, std::memory_order_release);
+        }
+    };
+    auto scanner = [&](int q) {
+        for (int64_t k = 0; k < nblk; ++k) {
+            BlockLists &bl = ring[k % R];
+            int spins = 0;
+            while (bl.ready.load(std::memory_order_acquire) != k) pause(&spins);
+            fits[q]->scan(ListedBalls{bl}, order);
+            if (fits[q]->finished()) break;
+            at[q].store(k + 1, std::memory_order_release);
+        }
+        at[q].store(nblk, std::memory_order_release);
+    };
+    std::vector<std::thread> th;
+    for (int w = 0; w < nw; ++w) th.emplace_back(lister);
+    for (int q = 1; q < nf; ++q) th.emplace_back(scanner, q);
+    scanner(0);
+    for (auto &x : th) x.join();
 }
 
 }  // namespace
 
 void vne::greedy_color_multi(int64_t n, const int32_t *rp, const int32_t *ci, const int32_t *ds, int nd,
-                             int32_t *const *colors_out, int32_t *n_colors) {
-    std::vector<int32_t> deg(n);
+                             int32_t *const *colors_out, int32_t *n_colors,
+                             const std::function<void(int)> &done) {
+    auto deliver = [&](int q, const std::vector<int32_t> &color, int32_t ncol) {
+        std::copy(color.begin(), color.end(), colors_out[q]);
+        n_colors[q] = ncol;
+        if (done) done(q);
+    };
+    // visiting order by counting the degrees
+    std::vector<int32_t> deg(n), order(n);
+    int32_t dmost = 0;
     for (int64_t i = 0; i < n; ++i) {
         int32_t c = 0;
         for (int32_t p = rp[i]; p < rp[i + 1]; ++p) c += (ci[p] != i);
         deg[i] = c;
+        dmost = std::max(dmost, c);
     }
-    std::vector<int32_t> order(n);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int32_t a, int32_t b) { return deg[a] > deg[b]; });
+    std::vector<int64_t> place((size_t)dmost + 2, 0);
+    for (int64_t i = 0; i < n; ++i) place[dmost - deg[i] + 1]++;
+    for (int32_t q = 0; q <= dmost; ++q) place[q + 1] += place[q];
+    for (int64_t i = 0; i < n; ++i) order[place[dmost - deg[i]]++] = (int32_t)i;
 
-    // half-depth balls for every distance
+    // half-depth balls for every distance; those whose balls are rows scan
+    // them beside the listing of the others
     std::vector<BallFit> ball(nd);
-    std::vector<BallFit *> bp;
+    std::vector<BallFit *> listed;
+    std::vector<std::thread> beside;
     int32_t depth = 1;                         // the deepest ball any distance needs
     for (int q = 0; q < nd; ++q) {
         ball[q].init(n, ds[q]);
-        bp.push_back(&ball[q]);
-        depth = std::max(depth, ds[q] - ds[q] / 2);
+        if (ball[q].a > 1) {
+            listed.push_back(&ball[q]);
+            depth = std::max(depth, ball[q].a);
+        }
     }
-    run_pipeline(n, rp, ci, order, depth, nullptr, bp);
+    const RowBalls rows{n, rp, ci};
+    for (int q = 0; q < nd; ++q) {
+        if (ball[q].a > 1) continue;
+        auto work = [&, q]() {
+            ball[q].scan(rows, order);
+            if (!ball[q].overflow) deliver(q, ball[q].color, ball[q].ncol);
+        };
+        if (nd > 1 && color_threads(n) > 1) beside.emplace_back(work);
+        else work();
+    }
+    if (!listed.empty()) run_pipeline(n, rp, ci, order, depth, nullptr, listed);
+    for (int q = 0; q < nd; ++q)
+        if (ball[q].a > 1 && !ball[q].overflow) deliver(q, ball[q].color, ball[q].ncol);
+    for (auto &x : beside) x.join();
 
     // distances whose colours outgrew the bitsets: earlier neighbours
     std::vector<DirectFit> direct;
@@ -383,23 +441,13 @@ void vne::greedy_color_multi(int64_t n, const int32_t *rp, const int32_t *ci, co
         }
         run_pipeline(n, rp, ci, order, dmax, pos.data(), dp);
     }
-    size_t r = 0;
-    for (int q = 0; q < nd; ++q) {
-        if (ball[q].overflow) {
-            std::copy(direct[r].color.begin(), direct[r].color.end(), colors_out[q]);
-            n_colors[q] = direct[r].ncol;
-            ++r;
-        } else {
-            std::copy(ball[q].color.begin(), ball[q].color.end(), colors_out[q]);
-            n_colors[q] = ball[q].ncol;
-        }
-    }
+    for (size_t r = 0; r < redo.size(); ++r) deliver(redo[r], direct[r].color, direct[r].ncol);
 }
 
 int32_t vne::greedy_color(int64_t n, const int32_t *rp, const int32_t *ci, int32_t d, int32_t *colors_out) {
     int32_t ncol = 0;
     int32_t *out[1] = {colors_out};
-    greedy_color_multi(n, rp, ci, &d, 1, out, &ncol);
+    greedy_color_multi(n, rp, ci, &d, 1, out, &ncol, nullptr);
     return ncol;
 }
 
