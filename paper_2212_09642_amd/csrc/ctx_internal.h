@@ -46,7 +46,7 @@ struct Plan {
     // the running-column count and its pinned host copy; the step loop is
     // captured chunk by chunk (steps up to one check), keyed by (schedule,
     // tile, first step of the chunk)
-    DevBuf col_tol, col_stop, bound_lo, bound_hi, adapt_args, remaining;
+    DevBuf col_tol, col_stop, bound_lo, bound_hi, adapt_args;
     int32_t *h_remaining = nullptr;
     std::vector<char> h_adapt;
     std::map<std::tuple<int, int, int>, hipGraphExec_t> chunk_exec;
@@ -242,7 +242,21 @@ vne_status hutchpp_run(vne_ctx *c, GraphSet *set, int nr, int nh, int g_col0, in
 vne_status check_mode(vne_ctx *c, uint32_t mode);
 void free_plan(vne_ctx *c, Plan *p);
 void free_set(vne_ctx *c, GraphSet *s);
-vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne_result *out, Plan *extra);
+// Device arrays of a plan to its pinned staging buffer (`at`, valid until the
+// next call for the plan), and with `estimates` the estimates: formed
+// (combine_kind >= 0) or from p->estimate (-1).  Waits for the stream.
+struct ResultPart {
+    const void *src;
+    size_t bytes;                    // a multiple of 4
+    const void *at = nullptr;
+};
+vne_status stage_room(vne_ctx *c, Plan *p, size_t bytes);
+vne_status fetch_results(vne_ctx *c, Plan *p, ResultPart *parts, int n, int combine_kind, double **estimates);
+// results of a plan's run to the caller; combine_kind >= 0: the estimates are
+// formed too (-1: they are in p->estimate)
+vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne_result *out, Plan *extra,
+                    int combine_kind);
+constexpr size_t kCollectBytes = 1 << 20;
 
 // On-chip runs (resident_run.hip): whole Lanczos loops inside workgroups.
 // The layout of one graph's on-chip run and its columns per workgroup, or

@@ -257,6 +257,22 @@ hipError_t launch_combine(const double *psi, int32_t m, int32_t kind, int32_t n_
 hipError_t launch_combine_graphs(const double *psi, int32_t ld, const int32_t *graph_m, int32_t n_graphs,
                                  int32_t kind, double *estimates, hipStream_t s);
 
+// Results into pinned host memory in one launch: up to kCollectParts arrays
+// of 32-bit words, and (kind >= 0) the estimates as launch_combine_graphs has
+// them.
+constexpr int kCollectParts = 8;
+struct CollectArgs {
+    const uint32_t *src[kCollectParts];
+    uint32_t *dst[kCollectParts];
+    int32_t words[kCollectParts];
+    int32_t parts;
+    const double *psi;
+    int32_t ld, kind, n_graphs;
+    const int32_t *graph_m;
+    double *estimates;
+};
+hipError_t launch_collect(const CollectArgs &a, hipStream_t s);
+
 // Y[i*ldy + c] = sqrt(norm2[c]) * sum_j S[j*m + c] Vstore[j][i*ldv + c]  (m <= 128)
 hipError_t launch_reconstruct(const void *Vstore, bool fp64, int64_t step_stride, int32_t ldv,
                               const double *S, const double *norm2, int32_t k, int32_t n,

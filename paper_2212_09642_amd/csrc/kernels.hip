@@ -2216,15 +2216,42 @@ __global__ void __launch_bounds__(256) k_combine(const double *psi, int32_t m, i
     }
 }
 
-__global__ void __launch_bounds__(256) k_combine_graphs(const double *psi, int32_t ld, const int32_t *graph_m,
-                                                        int32_t kind, double *estimates) {
+__device__ __forceinline__ void combine_graph(const double *psi, int32_t ld, const int32_t *graph_m, int32_t kind,
+                                              double *estimates, int g) {
     __shared__ double sh[256];
-    const int g = blockIdx.x;
     const int mg = graph_m[g];
     double b = 0.0;
     for (int c = threadIdx.x; c < mg; c += 256) b += psi[(int64_t)g * ld + c];
     b = block_sum_256(b, sh);
     if (threadIdx.x == 0) estimates[g] = kind == 1 ? b : (mg > 0 ? b / (double)mg : 0.0);
+}
+
+__global__ void __launch_bounds__(256) k_combine_graphs(const double *psi, int32_t ld, const int32_t *graph_m,
+                                                        int32_t kind, double *estimates) {
+    combine_graph(psi, ld, graph_m, kind, estimates, blockIdx.x);
+}
+
+// The end of a call: its estimates (a block a graph), and the other blocks
+// write its results to pinned host memory.  A combining launch and a copy per
+// array were 16 us of a 77 us estimate (1000 rows, 5 arrays), each the time
+// of a launch and not of its bytes.
+__global__ void __launch_bounds__(256) k_collect(CollectArgs a) {
+    const int combining = a.kind >= 0 ? a.n_graphs : 0;
+    if ((int)blockIdx.x < combining) {
+        combine_graph(a.psi, a.ld, a.graph_m, a.kind, a.estimates, blockIdx.x);
+        return;
+    }
+    const int first = ((int)blockIdx.x - combining) * 256 + threadIdx.x, stride = (gridDim.x - combining) * 256;
+    for (int q = 0; q < a.parts; ++q)
+        for (int t = first; t < a.words[q]; t += stride) a.dst[q][t] = a.src[q][t];
+}
+
+hipError_t launch_collect(const CollectArgs &a, hipStream_t s) {
+    int64_t words = 0;
+    for (int q = 0; q < a.parts; ++q) words += a.words[q];
+    const int copying = (int)std::clamp<int64_t>((words + 1023) / 1024, 1, 256);
+    hipLaunchKernelGGL(k_collect, dim3((a.kind >= 0 ? a.n_graphs : 0) + copying), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_combine_graphs(const double *psi, int32_t ld, const int32_t *graph_m, int32_t n_graphs,

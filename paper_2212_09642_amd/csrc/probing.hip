@@ -54,8 +54,11 @@ vne_status adaptive_run(vne_ctx *c, GraphSet *set, const vne_probes *pr, int k_m
     int combine_kind = 0;
     VNE_TRY(make_probe_spec(c, set, p, pr, m, fp64, &ps, &combine_kind));
     if (!p->col_tol.p) VNE_TRY(dev_alloc(c, &p->col_tol, (size_t)p->m_pad * 8));
-    HIP_TRY(c, hipMemcpyAsync(p->col_tol.p, tol, (size_t)m * 8, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    // (through the plan's staging buffer, which is written again only by the
+    // end of this run: no wait here)
+    VNE_TRY(stage_room(c, p, (size_t)m * 8));
+    std::memcpy(p->h_stage, tol, (size_t)m * 8);
+    HIP_TRY(c, hipMemcpyAsync(p->col_tol.p, p->h_stage, (size_t)m * 8, hipMemcpyHostToDevice, c->stream));
     VNE_TRY(autotune(c, set, p, ps, desing));
     RunOpts o;
     o.adaptive = true;
@@ -64,24 +67,28 @@ vne_status adaptive_run(vne_ctx *c, GraphSet *set, const vne_probes *pr, int k_m
     o.n_grid = n_grid;
     o.estimate = estimate;
     VNE_TRY(run_lanczos(c, set, p, ps, desing, o));
-    HIP_TRY(c, launch_combine_graphs((const double *)p->psi.p, p->m_pad, (const int32_t *)p->graph_m.p, 1,
-                                     combine_kind, (double *)p->estimate.p, c->stream));
-    hipStream_t s = c->stream;
-    po->psi.assign(m, 0.0);
-    po->steps.assign(m, 0);
-    int32_t fl = 0;
-    HIP_TRY(c, hipMemcpyAsync(&po->estimate, p->estimate.p, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipMemcpyAsync(po->psi.data(), p->psi.p, (size_t)m * 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipMemcpyAsync(po->steps.data(), p->col_stop.p, (size_t)m * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipMemcpyAsync(&fl, p->flags.p, 4, hipMemcpyDeviceToHost, s));
+    const size_t mk = (size_t)m * p->k * 8;
+    ResultPart parts[7] = {{p->psi.p, (size_t)m * 8},
+                           {p->col_stop.p, (size_t)m * 4},
+                           {p->flags.p, 4},
+                           {p->alpha.p, out && out->alpha ? mk : 0},
+                           {p->beta.p, out && out->beta ? mk : 0},
+                           {p->k_eff.p, out && out->k_eff ? (size_t)m * 4 : 0},
+                           {p->norm2.p, out && out->norm2 ? (size_t)m * 8 : 0}};
+    double *est = nullptr;
+    VNE_TRY(fetch_results(c, p, parts, 7, combine_kind, &est));
+    po->estimate = est[0];
+    const double *psi = (const double *)parts[0].at;
+    const int32_t *steps = (const int32_t *)parts[1].at;
+    po->psi.assign(psi, psi + m);
+    po->steps.assign(steps, steps + m);
+    const int32_t fl = *(const int32_t *)parts[2].at;
     if (out) {
-        const size_t mk = (size_t)m * p->k * 8;
-        if (out->alpha) HIP_TRY(c, hipMemcpyAsync(out->alpha, p->alpha.p, mk, hipMemcpyDeviceToHost, s));
-        if (out->beta) HIP_TRY(c, hipMemcpyAsync(out->beta, p->beta.p, mk, hipMemcpyDeviceToHost, s));
-        if (out->k_eff) HIP_TRY(c, hipMemcpyAsync(out->k_eff, p->k_eff.p, (size_t)m * 4, hipMemcpyDeviceToHost, s));
-        if (out->norm2) HIP_TRY(c, hipMemcpyAsync(out->norm2, p->norm2.p, (size_t)m * 8, hipMemcpyDeviceToHost, s));
+        if (out->alpha) std::memcpy(out->alpha, parts[3].at, mk);
+        if (out->beta) std::memcpy(out->beta, parts[4].at, mk);
+        if (out->k_eff) std::memcpy(out->k_eff, parts[5].at, (size_t)m * 4);
+        if (out->norm2) std::memcpy(out->norm2, parts[6].at, (size_t)m * 8);
     }
-    HIP_TRY(c, hipStreamSynchronize(s));
     if (c->timing) VNE_TRY(collect_timing(c));
     VNE_TRY(check_flags(c, fl));
     po->steps_run = p->steps_run;

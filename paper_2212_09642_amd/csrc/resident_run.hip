@@ -540,17 +540,12 @@ vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_
     HIP_TRY(c, launch_quadrature((const double *)p->alpha.p, (const double *)p->beta.p, (const int32_t *)p->k_eff.p,
                                  (const double *)p->norm2.p, p->k, p->k, p->G * p->m_pad, (double *)p->psi.p,
                                  (int32_t *)p->flags.p, c->stream, fp64));
-    HIP_TRY(c, launch_combine_graphs((const double *)p->psi.p, p->m_pad, (const int32_t *)p->graph_m.p, p->G,
-                                     b.combine, (double *)p->estimate.p, c->stream));
     if (!lp) {
         c->last_tile = b.cols[0];
         c->last_m_pad = p->m_pad;
     }
-    if (lp)
-        HIP_TRY(c, launch_combine_graphs((const double *)lp->psi.p, lp->m_pad, (const int32_t *)lp->graph_m.p, lp->G,
-                                         lcombine, (double *)lp->estimate.p, c->stream));
-    const vne_status st = copy_out(c, p, ts.ms.data(), ts.ks.data(), ts.out.data(), nullptr);
-    const vne_status sl = lp ? copy_out(c, lp, tl.ms.data(), tl.ks.data(), tl.out.data(), nullptr) : VNE_OK;
+    const vne_status st = copy_out(c, p, ts.ms.data(), ts.ks.data(), ts.out.data(), nullptr, b.combine);
+    const vne_status sl = lp ? copy_out(c, lp, tl.ms.data(), tl.ks.data(), tl.out.data(), nullptr, lcombine) : VNE_OK;
     for (size_t i = 0; i < small.size(); ++i) out[small[i]].estimate = ts.out[i].estimate;
     for (size_t i = 0; i < large.size(); ++i) out[large[i]].estimate = tl.out[i].estimate;
     VNE_TRY(st);

@@ -101,7 +101,7 @@ void free_plan(vne_ctx *c, Plan *p) {
                      &p->estimate, &p->flags, &p->partials, &p->level2, &p->probe_part, &p->seg_acc,
                      &p->long_part, &p->colors, &p->dense, &p->graph_k, &p->graph_m, &p->seeds,
                      &p->S, &p->B, &p->gram_part, &p->gram, &p->rinv, &p->rot, &p->col_tol, &p->col_stop,
-                     &p->bound_lo, &p->bound_hi, &p->adapt_args, &p->remaining, &p->res_args};
+                     &p->bound_lo, &p->bound_hi, &p->adapt_args, &p->res_args};
     for (DevBuf *b : all) dev_free(c, b);
 }
 
@@ -608,11 +608,10 @@ vne_status run_lanczos(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, 
         if (!p->bound_lo.p) VNE_TRY(dev_alloc(c, &p->bound_lo, (size_t)p->m_pad * 8));
         if (!p->bound_hi.p) VNE_TRY(dev_alloc(c, &p->bound_hi, (size_t)p->m_pad * 8));
         if (!p->adapt_args.p) VNE_TRY(dev_alloc(c, &p->adapt_args, nb));
-        if (!p->remaining.p) VNE_TRY(dev_alloc(c, &p->remaining, 4));
         if (!p->col_tol.p) return fail(c, VNE_EINVAL, "per-column tolerances not set");
         if (!p->h_remaining) HIP_TRY(c, hipHostMalloc((void **)&p->h_remaining, 4, hipHostMallocDefault));
-        p->h_adapt.assign(nb, 0);
-        BoundArgs *hb = (BoundArgs *)p->h_adapt.data();
+        std::vector<char> adapt(nb, 0);
+        BoundArgs *hb = (BoundArgs *)adapt.data();
         ColStopArgs *hs = (ColStopArgs *)(hb + K + 1);
         BoundArgs *db = (BoundArgs *)p->adapt_args.p;
         ColStopArgs *ds = (ColStopArgs *)(db + K + 1);
@@ -640,9 +639,14 @@ vne_status run_lanczos(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, 
             q.col_stop = (int32_t *)p->col_stop.p;
             q.m = M;
             q.step = j;
-            q.remaining = (int32_t *)p->remaining.p;
+            q.remaining = p->h_remaining;      // (pinned: read once the stream is idle)
         }
-        HIP_TRY(c, hipMemcpyAsync(p->adapt_args.p, p->h_adapt.data(), nb, hipMemcpyHostToDevice, c->stream));
+        if (p->h_adapt != adapt) {             // (uploaded only when they change, as above)
+            p->h_adapt.clear();
+            HIP_TRY(c, hipMemcpyAsync(p->adapt_args.p, adapt.data(), nb, hipMemcpyHostToDevice, c->stream));
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+            p->h_adapt.swap(adapt);
+        }
         HIP_TRY(c, hipMemsetAsync(p->col_stop.p, 0, (size_t)p->m_pad * 4, c->stream));
         // done columns: their tiles and normalize groups are skipped, their
         // coefficients kept (the quadrature takes the stop step's);
@@ -689,7 +693,6 @@ vne_status run_lanczos(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, 
             }
             ran = ch.j1;
             if (ch.check) {
-                HIP_TRY(c, hipMemcpyAsync(p->h_remaining, p->remaining.p, 4, hipMemcpyDeviceToHost, c->stream));
                 HIP_TRY(c, hipStreamSynchronize(c->stream));
                 if (*p->h_remaining == 0) break;
             }
@@ -874,8 +877,66 @@ vne_status check_flags(vne_ctx *c, int32_t fl) {
 // Results of every graph of the plan: one device-to-host copy per array,
 // then scattered into out[q] (m[q] columns, k[q] steps).  Also reads the
 // flag word of the plan (and of extra, if given) and synchronises.
-vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne_result *out, Plan *extra) {
+vne_status stage_room(vne_ctx *c, Plan *p, size_t bytes) {
+    if (p->h_stage_bytes >= bytes) return VNE_OK;
+    if (p->h_stage) {
+        HIP_TRY(c, hipStreamSynchronize(c->stream));   // a copy may still read it
+        HIP_TRY(c, hipHostFree(p->h_stage));
+    }
+    p->h_stage = nullptr;
+    p->h_stage_bytes = 0;
+    HIP_TRY(c, hipHostMalloc(&p->h_stage, bytes, hipHostMallocDefault));
+    p->h_stage_bytes = bytes;
+    return VNE_OK;
+}
+
+vne_status fetch_results(vne_ctx *c, Plan *p, ResultPart *parts, int n, int combine_kind, double **estimates) {
     hipStream_t s = c->stream;
+    const size_t n_est = estimates ? (size_t)p->G * 8 : 0;
+    size_t need = n_est;
+    for (int q = 0; q < n; ++q) need += (parts[q].bytes + 7) / 8 * 8;
+    VNE_TRY(stage_room(c, p, need));
+    char *at = (char *)p->h_stage;
+    if (estimates) *estimates = (double *)at;
+    at += n_est;
+    for (int q = 0; q < n; ++q) {
+        parts[q].at = at;
+        at += (parts[q].bytes + 7) / 8 * 8;
+    }
+    // one launch up to the size at which copies take the copy engines
+    if (need <= kCollectBytes) {
+        CollectArgs a{};
+        auto part = [&](void *dst, const void *src, size_t bytes) {
+            if (bytes == 0) return;
+            a.src[a.parts] = (const uint32_t *)src;
+            a.dst[a.parts] = (uint32_t *)dst;
+            a.words[a.parts++] = (int32_t)(bytes / 4);
+        };
+        if (n + 1 > kCollectParts) return fail(c, VNE_EINVAL, "too many result arrays");
+        a.kind = combine_kind;
+        a.psi = (const double *)p->psi.p;
+        a.ld = p->m_pad;
+        a.n_graphs = p->G;
+        a.graph_m = (const int32_t *)p->graph_m.p;
+        a.estimates = (double *)p->h_stage;
+        if (combine_kind < 0) part(p->h_stage, p->estimate.p, n_est);
+        for (int q = 0; q < n; ++q) part((void *)parts[q].at, parts[q].src, parts[q].bytes);
+        HIP_TRY(c, launch_collect(a, s));
+    } else {
+        if (combine_kind >= 0)
+            HIP_TRY(c, launch_combine_graphs((const double *)p->psi.p, p->m_pad, (const int32_t *)p->graph_m.p, p->G,
+                                             combine_kind, (double *)p->estimate.p, s));
+        if (n_est) HIP_TRY(c, hipMemcpyAsync(p->h_stage, p->estimate.p, n_est, hipMemcpyDeviceToHost, s));
+        for (int q = 0; q < n; ++q)
+            if (parts[q].bytes > 0)
+                HIP_TRY(c, hipMemcpyAsync((void *)parts[q].at, parts[q].src, parts[q].bytes, hipMemcpyDeviceToHost, s));
+    }
+    HIP_TRY(c, hipStreamSynchronize(s));
+    return VNE_OK;
+}
+
+vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne_result *out, Plan *extra,
+                    int combine_kind) {
     const int G = p->G;
     const size_t cols = (size_t)G * p->m_pad;
     bool any_quad = false, any_alpha = false, any_beta = false, any_keff = false, any_norm = false;
@@ -886,33 +947,19 @@ vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne
         any_keff |= out[q].k_eff != nullptr;
         any_norm |= out[q].norm2 != nullptr;
     }
-    // every array goes into one pinned staging buffer of the plan, so the
-    // copies queue without waiting and the call synchronises once
-    const size_t n_est = (size_t)G, n_psi = any_quad ? cols : 0, n_nrm = any_norm ? cols : 0;
-    const size_t n_al = any_alpha ? cols * p->k : 0, n_be = any_beta ? cols * p->k : 0;
-    const size_t n_ke = any_keff ? cols : 0;
-    const size_t need = 8 * (n_est + n_psi + n_nrm + n_al + n_be) + 4 * n_ke + 8;
-    if (p->h_stage_bytes < need) {
-        if (p->h_stage) HIP_TRY(c, hipHostFree(p->h_stage));
-        p->h_stage = nullptr;
-        p->h_stage_bytes = 0;
-        HIP_TRY(c, hipHostMalloc(&p->h_stage, need, hipHostMallocDefault));
-        p->h_stage_bytes = need;
-    }
-    double *est = (double *)p->h_stage;
-    double *psi = est + n_est, *nrm = psi + n_psi, *al = nrm + n_nrm, *be = al + n_al;
-    int32_t *ke = (int32_t *)(be + n_be);
-    int32_t *fl = ke + n_ke;
-    fl[0] = fl[1] = 0;
-    HIP_TRY(c, hipMemcpyAsync(est, p->estimate.p, n_est * 8, hipMemcpyDeviceToHost, s));
-    if (n_psi) HIP_TRY(c, hipMemcpyAsync(psi, p->psi.p, n_psi * 8, hipMemcpyDeviceToHost, s));
-    if (n_nrm) HIP_TRY(c, hipMemcpyAsync(nrm, p->norm2.p, n_nrm * 8, hipMemcpyDeviceToHost, s));
-    if (n_ke) HIP_TRY(c, hipMemcpyAsync(ke, p->k_eff.p, n_ke * 4, hipMemcpyDeviceToHost, s));
-    if (n_al) HIP_TRY(c, hipMemcpyAsync(al, p->alpha.p, n_al * 8, hipMemcpyDeviceToHost, s));
-    if (n_be) HIP_TRY(c, hipMemcpyAsync(be, p->beta.p, n_be * 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipMemcpyAsync(&fl[0], p->flags.p, 4, hipMemcpyDeviceToHost, s));
-    if (extra) HIP_TRY(c, hipMemcpyAsync(&fl[1], extra->flags.p, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipStreamSynchronize(s));
+    ResultPart parts[7] = {{p->psi.p, any_quad ? cols * 8 : 0},
+                           {p->norm2.p, any_norm ? cols * 8 : 0},
+                           {p->k_eff.p, any_keff ? cols * 4 : 0},
+                           {p->alpha.p, any_alpha ? cols * p->k * 8 : 0},
+                           {p->beta.p, any_beta ? cols * p->k * 8 : 0},
+                           {p->flags.p, 4},
+                           {extra ? extra->flags.p : nullptr, extra ? (size_t)4 : 0}};
+    double *est = nullptr;
+    VNE_TRY(fetch_results(c, p, parts, 7, combine_kind, &est));
+    const double *psi = (const double *)parts[0].at, *nrm = (const double *)parts[1].at;
+    const int32_t *ke = (const int32_t *)parts[2].at;
+    const double *al = (const double *)parts[3].at, *be = (const double *)parts[4].at;
+    const int32_t fl = *(const int32_t *)parts[5].at | (extra ? *(const int32_t *)parts[6].at : 0);
     if (c->timing) VNE_TRY(collect_timing(c));
     for (int q = 0; q < G; ++q) {
         const size_t c0 = (size_t)q * p->m_pad;
@@ -926,7 +973,7 @@ vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne
             if (o.beta) std::memcpy(o.beta + (size_t)col * k[q], be + (c0 + col) * p->k, (size_t)k[q] * 8);
         }
     }
-    return check_flags(c, fl[0] | fl[1]);
+    return check_flags(c, fl);
 }
 
 vne_status hutchpp_run(vne_ctx *c, GraphSet *set, int nr, int nh, int g_col0, int k, uint64_t seed, bool fp64,
@@ -1028,7 +1075,7 @@ vne_status estimate_hutchpp(vne_ctx *c, GraphSet *set, const vne_probes *pr, int
     // the Hutchinson columns follow the sketch's in the hash (columns nr .. m - 1)
     VNE_TRY(hutchpp_run(c, set, nr, m - nr, nr, k, pr->seed, fp64, desing, &sk, &q));
     const int32_t mm = m, kk = k;
-    return copy_out(c, q, &mm, &kk, out, sk);
+    return copy_out(c, q, &mm, &kk, out, sk, -1);
 }
 
 // Probe spec of a set's queries (one probe kind): Rademacher seeds, or the
@@ -1137,9 +1184,7 @@ vne_status estimate_set(vne_ctx *c, GraphSet *set, const vne_probes *pr, const i
         VNE_TRY(autotune(c, set, p, ps, desing));
         VNE_TRY(run_lanczos(c, set, p, ps, desing));
     }
-    HIP_TRY(c, launch_combine_graphs((const double *)p->psi.p, p->m_pad, (const int32_t *)p->graph_m.p, G,
-                                     combine_kind, (double *)p->estimate.p, c->stream));
-    return copy_out(c, p, ms.data(), k_steps, out, nullptr);
+    return copy_out(c, p, ms.data(), k_steps, out, nullptr, combine_kind);
 }
 
 vne_status check_mode(vne_ctx *c, uint32_t mode) {
