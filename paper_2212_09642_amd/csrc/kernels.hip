@@ -437,8 +437,11 @@ __device__ __forceinline__ bool tile_live(const StepArgs &a, int tile0, int ntil
 // threads as alone.  With JT > 1 the lane groups of the JT tiles of one item
 // sit side by side in a wave: their gathers of one neighbour row are one
 // contiguous run of JT * MT columns (narrow tiles fill whole cache lines).
+// own_segs: the block's segments of long rows too (else long_block has them;
+// the rows keep the lane groups, and so the sums the order, that they have
+// beside the segments).
 template <typename T, int CPL, int LPR, bool FIRST, bool TWO, int JT = 1>
-__device__ __forceinline__ void step_block(const StepArgs &a, int b, int tile0,
+__device__ __forceinline__ void step_block(const StepArgs &a, int b, int tile0, bool own_segs,
                                            double (*red)[(kStepThreads / 64) * (64 / LPR) * CPL * LPR]) {
     static_assert(JT == 1 || LPR * JT <= 64, "the tiles of an item share a wave");
     using Core = StepCore<T, CPL, LPR, FIRST, TWO>;
@@ -502,13 +505,14 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int b, int tile0,
             x.p1 = __builtin_amdgcn_readfirstlane(x.p1);
         }
     };
-    Item cur = locate(gid);
+    const int t0 = own_segs || n_sb <= gid ? gid : gid + (n_sb - gid + NG - 1) / NG * NG;
+    Item cur = locate(t0);
     bool cur_skip;
-    settle(cur, cur_skip, gid);
+    settle(cur, cur_skip, t0);
     typename Core::template Idx<U> ix;
     core.template batch_fetch<U>(cur.row, cur.p0, cur.p1, ix);
-    Item nxt = locate(gid + NG);
-    for (int t = gid; t < total; t += NG) {
+    Item nxt = locate(t0 + NG);
+    for (int t = t0; t < total; t += NG) {
         int jj[U];
         T vv[U], pv[U][CPL], qv[U][CPL];
         const int cnt = min(U, cur.p1 - cur.p0);
@@ -540,7 +544,7 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int b, int tile0,
                 }
             } else {
                 // segment of a long row: its partial product is finished by
-                // k_long_rows after this kernel (the kernel boundary orders it)
+                // k_long_rows_slots after this kernel (the boundary orders it)
                 double *dst = a.seg_acc + (int64_t)cur.it * core.ld + core.c0;
 #pragma unroll
                 for (int k = 0; k < CPL; ++k) dst[k] = acc[k];
@@ -565,6 +569,95 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int b, int tile0,
     }
 }
 
+// A long row: adds the segment partial products in segment order and finishes
+// the row; its dot-product contributions go to a slot of its own.
+template <typename T, int CPL, int LPR, bool FIRST, bool TWO>
+__device__ __forceinline__ void finish_long_row(const StepArgs &a, int L,
+                                                const StepCore<T, CPL, LPR, FIRST, TWO> &core) {
+    const int first = a.long_first[L], nseg = a.long_nseg[L];
+    const int row = a.segs[first].row;
+    T pv[CPL], qv[CPL];
+    core.load_self(row, pv, qv);
+    double tot[CPL];
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) tot[k] = 0.0;
+    constexpr int UQ = 8;
+    int q = 0;
+    for (; q + UQ <= nseg; q += UQ) {
+        double buf[UQ][CPL];
+#pragma unroll
+        for (int u = 0; u < UQ; ++u) {
+            const double *src = a.seg_acc + (int64_t)(first + q + u) * core.ld + core.c0;
+#pragma unroll
+            for (int k = 0; k < CPL; ++k) buf[u][k] = src[k];
+        }
+#pragma unroll
+        for (int u = 0; u < UQ; ++u)
+#pragma unroll
+            for (int k = 0; k < CPL; ++k) tot[k] += buf[u][k];
+    }
+    for (; q < nseg; ++q) {
+        const double *src = a.seg_acc + (int64_t)(first + q) * core.ld + core.c0;
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) tot[k] += src[k];
+    }
+    double dvw[CPL], dww[CPL], dvv[CPL];
+    core.finish(row, pv, qv, tot, dvw, dww, dvv);
+    double *lp = a.long_part + (int64_t)L * 3 * core.ld + core.c0;
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) {
+        lp[k] = dvw[k];
+        lp[core.ld + k] = dww[k];
+        lp[2 * core.ld + k] = dvv[k];
+    }
+}
+
+// The long rows of block b, long_rows<LPR>() of them: their segments
+// (contiguous in segs) over the block's lane groups, then a lane group a row
+// adds and finishes.  A launch of its own for the second part was 5.5 to 8 us
+// a step, a tenth of a step of 5e4 rows; here it runs beside the other rows,
+// from the front of the grid, since a hub's segments are the longest chain of
+// the launch.  More rows keep the lane groups of a narrow tile busy; a wide
+// tile has fewer, and a block of several hubs (the oldest rows of a
+// preferential-attachment graph are its largest and are neighbours) would
+// outlast the step (BA n = 5e4, 64 columns, us a step: 43.9 with the
+// launch, 50.6 with four rows a block, 39.5 with one; BA n = 2e5, 16 columns
+// 56.1 and 48.2 with four).
+template <int LPR>
+constexpr int long_rows() { return LPR <= 4 ? 4 : LPR == 8 ? 2 : 1; }
+
+template <typename T, int CPL, int LPR, bool FIRST, bool TWO>
+__device__ __forceinline__ void long_block(const StepArgs &a, int b, int tile) {
+    using Core = StepCore<T, CPL, LPR, FIRST, TWO>;
+    constexpr int GPW = 64 / LPR;
+    constexpr int NG = (kStepThreads / 64) * GPW;
+    constexpr int kRows = long_rows<LPR>();
+    static_assert(NG >= kRows, "a lane group per row");
+    const int lane = threadIdx.x & 63;
+    const int gid = (threadIdx.x >> 6) * GPW + lane / LPR, gl = lane % LPR;
+    const int L0 = b * kRows, L1 = min(L0 + kRows, a.n_long);
+    if (L0 >= L1) return;
+    const int s1 = a.long_first[L1 - 1] + a.long_nseg[L1 - 1];
+    // (several graphs: the segments' products need nothing of the graph on the
+    // two-pass schedule)
+    const int L = min(L0 + gid, L1 - 1);
+    const Core core(a, tile, gl, a.long_graph ? a.long_graph[L] : 0);
+    for (int s = a.long_first[L0] + gid; s < s1; s += NG) {
+        const SegItem sg = a.segs[s];
+        typename Core::template Idx<Core::UM> x;
+        if (Core::kAhead) core.template batch_fetch<Core::UM>(sg.row, sg.p0, sg.p1, x);
+        double acc[CPL];
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) acc[k] = 0.0;
+        core.gather_from(sg.row, sg.p0, sg.p1, x, acc);
+        double *dst = a.seg_acc + (int64_t)s * core.ld + core.c0;
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) dst[k] = acc[k];
+    }
+    __syncthreads();
+    if (L0 + gid < L1) finish_long_row<T, CPL, LPR, FIRST, TWO>(a, L, core);
+}
+
 template <typename T, int CPL, int LPR, bool FIRST, bool TWO>
 __global__ void __launch_bounds__(kStepThreads) VNE_STEP_OCCUPANCY k_lanczos_step(StepArgs a) {
     constexpr int NG = (kStepThreads / 64) * (64 / LPR);
@@ -575,7 +668,12 @@ __global__ void __launch_bounds__(kStepThreads) VNE_STEP_OCCUPANCY k_lanczos_ste
     // (n_blocks is a multiple of 8)
     const int tile = a.tile_base + (int)blockIdx.y;
     if (a.col_stop && !tile_live(a, tile, 1, CPL * LPR)) return;
-    step_block<T, CPL, LPR, FIRST, TWO>(a, xcd_remap(blockIdx.x, a.n_blocks), tile, red);
+    const int n_front = gridDim.x - a.n_blocks;         // blocks of long rows (a multiple of 8)
+    if ((int)blockIdx.x < n_front) {
+        long_block<T, CPL, LPR, FIRST, TWO>(a, blockIdx.x, tile);
+        return;
+    }
+    step_block<T, CPL, LPR, FIRST, TWO>(a, xcd_remap(blockIdx.x - n_front, a.n_blocks), tile, n_front == 0, red);
 }
 
 // Several independent problems ("slots") in one launch: entry e = {slot,
@@ -604,7 +702,7 @@ __global__ void __launch_bounds__(kStepThreads) VNE_STEP_OCCUPANCY k_lanczos_ste
     const int4 e = map[xcd_remap(blockIdx.x, n_entries)];
     const StepArgs a = args[e.x];
     if (slot_stopped(a.stop_state, a.stop_uid, a.stop_count)) return;
-    step_block<T, CPL, LPR, false, true>(a, e.y, e.z, red);
+    step_block<T, CPL, LPR, false, true>(a, e.y, e.z, true, red);
 }
 
 // JT column tiles of one slot per block (JT * kStepThreads threads): entry
@@ -619,7 +717,7 @@ __global__ void __launch_bounds__(JT * kStepThreads) k_lanczos_step_groups(const
     const int4 e = map[xcd_remap(blockIdx.x, n_entries)];
     const StepArgs a = args[e.x];
     if (slot_stopped(a.stop_state, a.stop_uid, a.stop_count)) return;
-    step_block<T, CPL, LPR, false, true, JT>(a, e.y, e.z, red);
+    step_block<T, CPL, LPR, false, true, JT>(a, e.y, e.z, true, red);
 }
 
 // Normalize pass of the slots: entry {slot, work block, tile} writes v_j on
@@ -652,55 +750,17 @@ __global__ void __launch_bounds__(256) k_normalize_slots(const StepArgs *args, c
     }
 }
 
-// Long rows: add the segment partial products in segment order and finish
-// the row; its dot-product contributions go to a slot of its own.
+// A lane group per long row of the group (several graphs on the lazy
+// schedule, and slots).
 template <typename T, int CPL, int LPR, bool FIRST, bool TWO>
 __device__ __forceinline__ void long_rows_group(const StepArgs &a, int group, int tile) {
-    using Core = StepCore<T, CPL, LPR, FIRST, TWO>;
     constexpr int GPW = 64 / LPR;
     constexpr int NG = 4 * GPW;
     const int lane = threadIdx.x & 63;
-    const int grp = lane / LPR;
-    const int gl = lane % LPR;
-    const int L = group * NG + (threadIdx.x >> 6) * GPW + grp;
+    const int L = group * NG + (threadIdx.x >> 6) * GPW + lane / LPR;
     if (L >= a.n_long) return;
-    const Core core(a, tile, gl, a.long_graph ? a.long_graph[L] : 0);
-    const int first = a.long_first[L], nseg = a.long_nseg[L];
-    const int row = a.segs[first].row;
-    double tot[CPL];
-#pragma unroll
-    for (int k = 0; k < CPL; ++k) tot[k] = 0.0;
-    constexpr int UQ = 8;
-    int q = 0;
-    for (; q + UQ <= nseg; q += UQ) {
-        double buf[UQ][CPL];
-#pragma unroll
-        for (int u = 0; u < UQ; ++u) {
-            const double *src = a.seg_acc + (int64_t)(first + q + u) * core.ld + core.c0;
-#pragma unroll
-            for (int k = 0; k < CPL; ++k) buf[u][k] = src[k];
-        }
-#pragma unroll
-        for (int u = 0; u < UQ; ++u)
-#pragma unroll
-            for (int k = 0; k < CPL; ++k) tot[k] += buf[u][k];
-    }
-    for (; q < nseg; ++q) {
-        const double *src = a.seg_acc + (int64_t)(first + q) * core.ld + core.c0;
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) tot[k] += src[k];
-    }
-    T pv[CPL], qv[CPL];
-    core.load_self(row, pv, qv);
-    double dvw[CPL], dww[CPL], dvv[CPL];
-    core.finish(row, pv, qv, tot, dvw, dww, dvv);
-    double *lp = a.long_part + (int64_t)L * 3 * core.ld + core.c0;
-#pragma unroll
-    for (int k = 0; k < CPL; ++k) {
-        lp[k] = dvw[k];
-        lp[core.ld + k] = dww[k];
-        lp[2 * core.ld + k] = dvv[k];
-    }
+    finish_long_row<T, CPL, LPR, FIRST, TWO>(
+        a, L, StepCore<T, CPL, LPR, FIRST, TWO>(a, tile, lane % LPR, a.long_graph ? a.long_graph[L] : 0));
 }
 
 template <typename T, int CPL, int LPR, bool FIRST, bool TWO>
@@ -775,9 +835,13 @@ static void launch_step_k(const StepArgs &a, hipStream_t s) {
         const unsigned nb = (unsigned)std::min<int64_t>((groups + 255) / 256, 8192);
         hipLaunchKernelGGL((k_normalize<T, CPL, FIRST>), dim3(nb), dim3(256), 0, s, a);
     }
-    dim3 grid(a.n_blocks, a.n_tiles);
+    // blocks of long rows at the front, unless rows of several graphs would
+    // meet in one (the lazy schedule needs its graph's scalars throughout)
+    const bool front = a.n_long > 0 && (TWO || !a.block_graph);
+    const int n_front = front ? ((a.n_long + long_rows<LPR>() - 1) / long_rows<LPR>() + 7) / 8 * 8 : 0;
+    dim3 grid(n_front + a.n_blocks, a.n_tiles);
     hipLaunchKernelGGL((k_lanczos_step<T, CPL, LPR, FIRST, TWO>), grid, dim3(kStepThreads), 0, s, a);
-    if (a.n_long > 0) {
+    if (a.n_long > 0 && !front) {
         constexpr int NG = 4 * (64 / LPR);
         dim3 lg((a.n_long + NG - 1) / NG, a.n_tiles);
         hipLaunchKernelGGL((k_long_rows<T, CPL, LPR, FIRST, TWO>), lg, dim3(256), 0, s, a);
