@@ -177,8 +177,17 @@ struct ProbeArgs {
     const int32_t *graph_m;            // [G]
     int32_t n_graphs;
     int32_t *flags;                    // bit 0 set for a start vector whose norm is not finite
+    // serving slots: v_0 (laid out as P_out) is written as zeros, and n_state
+    // stop records are cleared
+    void *zero_rows;
+    int2 *zero_state;
+    int32_t n_state;
 };
 hipError_t launch_probe(const ProbeArgs &a, bool fp64, hipStream_t s);
+// Several probe blocks of one graph each at once (args in device memory):
+// block_map entries {job, probe block}, column_map entries {job, column}.
+hipError_t launch_probe_slots(const ProbeArgs *args, const int2 *block_map, int32_t n_blocks, const int2 *column_map,
+                              int32_t n_columns, bool fp64, hipStream_t s);
 
 // raw +-1 Rademacher block into out[i*ld + off + c], c < m (no centring)
 hipError_t launch_rademacher_fill(void *out, bool fp64, int32_t n, int32_t m, int32_t ld, int32_t off,
@@ -195,6 +204,39 @@ hipError_t launch_quadrature(const double *alpha, const double *beta, const int3
                              const double *norm2, int32_t k, int32_t steps, int32_t m, double *psi,
                              int32_t *flags, hipStream_t s, bool fp64, const int2 *stop = nullptr,
                              int32_t uid = 0, const int32_t *col_stop = nullptr, int32_t *steps_out = nullptr);
+// The quadratures of several problems in one launch, arguments by value (jobs
+// of as launch_quadrature's; first[j]: blocks before job j's).
+constexpr int kQuadJobs = 32;
+struct QuadJob {
+    const double *alpha, *beta;
+    const int32_t *k_eff;
+    const double *norm2;
+    double *psi;
+    int32_t *flags;
+    const int2 *stop;
+    int32_t *steps_out;
+    int32_t k, steps, m, uid;
+};
+struct QuadJobs {
+    QuadJob job[kQuadJobs];
+    int32_t first[kQuadJobs + 1];
+    int32_t n;
+};
+hipError_t launch_quadrature_jobs(const QuadJobs &a, bool fp64, hipStream_t s);
+// Forms of several queries to their pinned buffers: n forms at host[0], and
+// at host[tail] the flags word (mean: the mean of the forms at host[tail - 1],
+// the flags and the word after them).
+struct FormsJob {
+    const double *psi;
+    const int32_t *flags;
+    double *host;
+    int32_t n, tail, mean;
+};
+struct FormsJobs {
+    FormsJob job[kQuadJobs];
+    int32_t n;
+};
+hipError_t launch_forms_jobs(const FormsJobs &a, hipStream_t s);
 // f(T) e1 for every column (rows >= k_eff are 0), step-major: S[r*m + c]; rot_scratch
 // holds rot_capacity(k) recorded rotations (24 bytes each) per column
 __host__ __device__ int64_t rot_capacity(int32_t k);

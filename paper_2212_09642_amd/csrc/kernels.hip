@@ -1280,16 +1280,15 @@ __device__ __forceinline__ double probe_value(const ProbeArgs &a, int g, int64_t
 // Pass 1 sums every column; pass 2 writes P_1 = b - mean (element type of the
 // mode) and sums the squares of the stored values.
 template <typename T, int PASS>
-__global__ void __launch_bounds__(256) k_probe(ProbeArgs a) {
+__device__ __forceinline__ void probe_block(const ProbeArgs &a, int b) {
     __shared__ double sh[256];
     const int rows_per = 256 / a.mt;
     const int cc = threadIdx.x % a.mt, rr = threadIdx.x / a.mt;
     // a tile width that does not divide 256 leaves the last threads idle
     const bool active = rr < rows_per;
-    const int b = blockIdx.x;
     const int g = a.block_graph ? a.block_graph[b] : 0;
     const int64_t r0 = a.block_row_begin[b], r1 = a.block_row_begin[b + 1];
-    T *P = static_cast<T *>(a.P_out);
+    T *P = static_cast<T *>(a.P_out), *Z = static_cast<T *>(a.zero_rows);
     const int64_t ld = a.ld_out > 0 ? a.ld_out : a.m_pad;
     for (int t0 = 0; t0 < a.m_pad; t0 += a.mt) {
         const int c = t0 + cc;
@@ -1302,6 +1301,7 @@ __global__ void __launch_bounds__(256) k_probe(ProbeArgs a) {
             } else {
                 const T cv = (T)(v - mu);
                 P[i * ld + c] = cv;
+                if (Z) Z[i * ld + c] = (T)0;
                 acc += (double)cv * (double)cv;
             }
         }
@@ -1317,17 +1317,23 @@ __global__ void __launch_bounds__(256) k_probe(ProbeArgs a) {
     }
 }
 
-// (g, c) per block: adds graph g's probe-block partials in order.
+template <typename T, int PASS>
+__global__ void __launch_bounds__(256) k_probe(ProbeArgs a) {
+    probe_block<T, PASS>(a, blockIdx.x);
+}
+
+// column c of graph g: adds the graph's probe-block partials in order
 template <int PASS>
-__global__ void __launch_bounds__(256) k_probe_reduce(ProbeArgs a) {
+__device__ __forceinline__ void probe_column(const ProbeArgs &a, int g, int c) {
     __shared__ double sh[256];
-    const int g = blockIdx.x / a.m_pad, c = blockIdx.x % a.m_pad;
     const int64_t gc = (int64_t)g * a.m_pad + c;
     double sum = 0.0;
     for (int bb = a.graph_block_begin[g] + threadIdx.x; bb < a.graph_block_begin[g + 1]; bb += 256)
         sum += a.partials[(int64_t)bb * a.m_pad + c];
     sum = block_sum_256(sum, sh);
     if (threadIdx.x != 0) return;
+    if (PASS == 2 && a.zero_state && c == 0)
+        for (int i = 0; i < a.n_state; ++i) a.zero_state[i] = make_int2(0, 0);
     const int mg = a.graph_m ? a.graph_m[g] : a.m;
     const int kg = a.graph_k ? a.graph_k[g] : a.k;
     if (PASS == 1) {
@@ -1347,6 +1353,45 @@ __global__ void __launch_bounds__(256) k_probe_reduce(ProbeArgs a) {
             a.k_eff[gc] = 0;
         }
     }
+}
+
+template <int PASS>
+__global__ void __launch_bounds__(256) k_probe_reduce(ProbeArgs a) {
+    probe_column<PASS>(a, blockIdx.x / a.m_pad, blockIdx.x % a.m_pad);
+}
+
+// The blocks and columns of several probe blocks, which a server's tick starts
+// together: launched one by one they were four kernels and two fills a task,
+// each the time of a launch (a burst of 32 queries starts 150 tasks).
+template <typename T, int PASS>
+__global__ void __launch_bounds__(256) k_probe_slots(const ProbeArgs *args, const int2 *map) {
+    const int2 e = map[blockIdx.x];
+    const ProbeArgs a = args[e.x];
+    probe_block<T, PASS>(a, e.y);
+}
+
+template <int PASS>
+__global__ void __launch_bounds__(256) k_probe_reduce_slots(const ProbeArgs *args, const int2 *map) {
+    const int2 e = map[blockIdx.x];
+    const ProbeArgs a = args[e.x];
+    probe_column<PASS>(a, 0, e.y);
+}
+
+template <typename T>
+static void launch_probe_slots_t(const ProbeArgs *args, const int2 *block_map, int32_t n_blocks,
+                                 const int2 *column_map, int32_t n_columns, hipStream_t s) {
+    hipLaunchKernelGGL((k_probe_slots<T, 1>), dim3(n_blocks), dim3(256), 0, s, args, block_map);
+    hipLaunchKernelGGL((k_probe_reduce_slots<1>), dim3(n_columns), dim3(256), 0, s, args, column_map);
+    hipLaunchKernelGGL((k_probe_slots<T, 2>), dim3(n_blocks), dim3(256), 0, s, args, block_map);
+    hipLaunchKernelGGL((k_probe_reduce_slots<2>), dim3(n_columns), dim3(256), 0, s, args, column_map);
+}
+
+hipError_t launch_probe_slots(const ProbeArgs *args, const int2 *block_map, int32_t n_blocks, const int2 *column_map,
+                              int32_t n_columns, bool fp64, hipStream_t s) {
+    if (n_blocks <= 0 || n_columns <= 0) return hipErrorInvalidValue;
+    if (fp64) launch_probe_slots_t<double>(args, block_map, n_blocks, column_map, n_columns, s);
+    else launch_probe_slots_t<float>(args, block_map, n_blocks, column_map, n_columns, s);
+    return hipGetLastError();
 }
 
 hipError_t launch_probe(const ProbeArgs &a, bool fp64, hipStream_t s) {
@@ -1707,14 +1752,12 @@ __device__ bool e1_fT_e1_integral(const LaneTri &t, int ke, int lane, int shift_
     return true;
 }
 
-__global__ void __launch_bounds__(256) k_quadrature(const double *alpha, const double *beta,
-                                                    const int32_t *k_eff, const double *norm2, int32_t k,
-                                                    int32_t steps, int32_t m, double *psi, int32_t *flags,
-                                                    const int2 *stop, int32_t uid, const int32_t *col_stop,
-                                                    int32_t shift_max, int32_t *steps_out) {
-    const int c = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+// column c of a problem, one wave
+__device__ __forceinline__ void quadrature_column(const double *alpha, const double *beta, const int32_t *k_eff,
+                                                  const double *norm2, int32_t k, int32_t steps, int c, double *psi,
+                                                  int32_t *flags, const int2 *stop, int32_t uid,
+                                                  const int32_t *col_stop, int32_t shift_max, int32_t *steps_out) {
     const int lane = threadIdx.x & 63;
-    if (c >= m) return;
     if (stop) {
         const int2 st = *stop;
         if (st.x == uid && st.y > 0) steps = min(steps, st.y);
@@ -1752,6 +1795,37 @@ __global__ void __launch_bounds__(256) k_quadrature(const double *alpha, const d
         if (st) atomicOr(flags, st);
     }
 }
+
+__global__ void __launch_bounds__(256) k_quadrature(const double *alpha, const double *beta,
+                                                    const int32_t *k_eff, const double *norm2, int32_t k,
+                                                    int32_t steps, int32_t m, double *psi, int32_t *flags,
+                                                    const int2 *stop, int32_t uid, const int32_t *col_stop,
+                                                    int32_t shift_max, int32_t *steps_out) {
+    const int c = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (c >= m) return;
+    quadrature_column(alpha, beta, k_eff, norm2, k, steps, c, psi, flags, stop, uid, col_stop, shift_max, steps_out);
+}
+
+// The members that end in one tick of a server together (10 us each, in turn,
+// whatever their columns).
+__global__ void __launch_bounds__(256) k_quadrature_jobs(QuadJobs a, int32_t shift_max) {
+    int j = 0;
+    while (j + 1 < a.n && (int)blockIdx.x >= a.first[j + 1]) ++j;
+    const QuadJob &q = a.job[j];
+    const int c = __builtin_amdgcn_readfirstlane((blockIdx.x - a.first[j]) * 4 + (threadIdx.x >> 6));
+    if (c >= q.m) return;
+    quadrature_column(q.alpha, q.beta, q.k_eff, q.norm2, q.k, q.steps, c, q.psi, q.flags, q.stop, q.uid, nullptr,
+                      shift_max, q.steps_out);
+}
+
+hipError_t launch_quadrature_jobs(const QuadJobs &a, bool fp64, hipStream_t s) {
+    if (a.n < 1 || a.n > kQuadJobs || a.first[a.n] < 1) return hipErrorInvalidValue;
+    for (int j = 0; j < a.n; ++j)
+        if (a.job[j].k > kMaxSteps || a.job[j].steps < 1 || a.job[j].steps > a.job[j].k) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_quadrature_jobs, dim3(a.first[a.n]), dim3(256), 0, s, a, fp64 ? 1 : 4);
+    return hipGetLastError();
+}
+
 
 // ---------------------------------------------------------------------------
 // A-posteriori error bracket of Theorem 4.8 for the polynomial Krylov method
@@ -2308,6 +2382,32 @@ __global__ void __launch_bounds__(256) k_collect(CollectArgs a) {
     const int first = ((int)blockIdx.x - combining) * 256 + threadIdx.x, stride = (gridDim.x - combining) * 256;
     for (int q = 0; q < a.parts; ++q)
         for (int t = first; t < a.words[q]; t += stride) a.dst[q][t] = a.src[q][t];
+}
+
+// a block per query: its forms (and their mean, as k_combine has it) and flags
+__global__ void __launch_bounds__(256) k_forms_jobs(FormsJobs a) {
+    __shared__ double sh[256];
+    const FormsJob &q = a.job[blockIdx.x];
+    double b = 0.0;
+    for (int c = threadIdx.x; c < q.n; c += 256) {
+        const double v = q.psi[c];
+        b += v;
+        q.host[c] = v;
+    }
+    b = block_sum_256(b, sh);
+    if (threadIdx.x != 0) return;
+    int32_t *fl = (int32_t *)(q.host + q.tail);
+    fl[0] = q.flags[0];
+    if (q.mean) {
+        q.host[q.tail - 1] = b / (double)q.n;
+        fl[1] = q.flags[1];
+    }
+}
+
+hipError_t launch_forms_jobs(const FormsJobs &a, hipStream_t s) {
+    if (a.n < 1 || a.n > kQuadJobs) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_forms_jobs, dim3(a.n), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_collect(const CollectArgs &a, hipStream_t s) {

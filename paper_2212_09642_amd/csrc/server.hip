@@ -179,7 +179,6 @@ public:
 
     char *arena_base() const { return (char *)arena_mem.p; }
     double *d_psi(const ServeQuery &q) const { return (double *)(arena_base() + q.off); }
-    double *d_est(const ServeQuery &q) const { return (double *)(arena_base() + q.off + rnd((size_t)psi_cap * 8)); }
     int32_t *d_flags(const ServeQuery &q) const {
         return (int32_t *)(arena_base() + q.off + rnd((size_t)psi_cap * 8) + 256);
     }
@@ -222,7 +221,51 @@ public:
         return e;
     }
 
+    // Work of the core's calls that is launched together: the probe blocks of
+    // started tasks at the next tick, the quadratures and result copies of
+    // ended members when the host next looks for a result (or at the tick).
+    // Whatever could touch the memory of pending work launches it first.
+    std::vector<ProbeArgs> probes;
+    QuadJobs quads{};
+    FormsJobs outs{};
+    std::vector<hipEvent_t> out_events;
+
+    vne_status flush_probes() {
+        for (const ProbeArgs &pa : probes) VNE_TRY(hip_err(launch_probe(pa, fp64, stream), "launch_probe"));
+        probes.clear();
+        return VNE_OK;
+    }
+
+    vne_status flush_results() {
+        if (quads.n > 0) VNE_TRY(hip_err(launch_quadrature_jobs(quads, fp64, stream), "launch_quadrature_jobs"));
+        quads.n = 0;
+        if (outs.n > 0) VNE_TRY(hip_err(launch_forms_jobs(outs, stream), "launch_forms_jobs"));
+        outs.n = 0;
+        for (hipEvent_t ev : out_events) VNE_TRY(hip_err(hipEventRecord(ev, stream), "hipEventRecord"));
+        out_events.clear();
+        return VNE_OK;
+    }
+
+    // before a query or its graph goes (an error is the next call's)
+    void flush() {
+        if (flush_results() != VNE_OK || flush_probes() != VNE_OK) {
+            quads.n = outs.n = 0;
+            out_events.clear();
+            probes.clear();
+        }
+    }
+
+    // the query's next copy: nothing is ready before its event is recorded
+    vne_status issue_forms(ServeQuery &q, int n, int tail, bool mean) {
+        if (outs.n == kQuadJobs) VNE_TRY(flush_results());
+        GpuQuery *x = gq(q);
+        outs.job[outs.n++] = FormsJob{d_psi(q), d_flags(q), x->h_buf, n, tail, mean ? 1 : 0};
+        out_events.push_back(x->ev);
+        return VNE_OK;
+    }
+
     vne_status open_query(ServeQuery &q) override {
+        VNE_TRY(flush_results());        // q's block may have been a task's
         GpuQuery *x = gq(q);
         x->h_buf = get_pinned();
         x->ev = get_event();
@@ -232,7 +275,7 @@ public:
 
     // Probe block of member i (the query's hash columns col0.., eq. (3.8))
     // into its columns of the slot.
-    vne_status member_probes(const ServeTask &t, const DevTask &d, int i, const ServeQuery &q) {
+    void member_probes(const ServeTask &t, const DevTask &d, int i, const ServeQuery &q) {
         const ServeMember &u = t.mem[i];
         const GraphSet *set = gq(q)->set;
         const size_t es = fp64 ? 8 : 4;
@@ -248,7 +291,7 @@ public:
         pa.keys = (const int64_t *)set->keys.p;
         pa.desing = desing ? 1 : 0;
         pa.P_out = d.P[0] + (size_t)u.c_off * es;
-        pa.partials = d.probe_part;
+        pa.partials = d.probe_part + (size_t)set->probe_blocks * u.c_off;
         pa.n_blocks = set->probe_blocks;
         pa.mean = d.mean + u.c_off;
         pa.norm2 = d.norm2 + u.c_off;
@@ -262,16 +305,17 @@ public:
         pa.graph_block_begin = (const int32_t *)set->probe_graph_begin.p;
         pa.graph_row_begin = (const int64_t *)set->graph_row_begin.p;
         pa.n_graphs = 1;
-        return hip_err(launch_probe(pa, fp64, stream), "launch_probe");
+        // v_0 = 0 and, with the first member, the stop records
+        pa.zero_rows = d.V[1] + (size_t)u.c_off * es;
+        pa.zero_state = i == 0 ? d.d_state : nullptr;
+        pa.n_state = t.n_mem;
+        probes.push_back(pa);
     }
 
     vne_status start_task(ServeTask &t, ServeQuery *const *qm) override {
         const DevTask d = dev(t, *qm[0]);
-        VNE_TRY(hip_err(hipMemsetAsync(d.d_state, 0, sizeof(int2) * t.n_mem, stream), "hipMemsetAsync"));
-        for (int i = 0; i < t.n_mem; ++i) VNE_TRY(member_probes(t, d, i, *qm[i]));
-        // zero v_0
-        return hip_err(hipMemsetAsync(d.V[1], 0, (size_t)gq(*qm[0])->set->n * t.m_pad * (fp64 ? 8 : 4), stream),
-                       "hipMemsetAsync");
+        for (int i = 0; i < t.n_mem; ++i) member_probes(t, d, i, *qm[i]);
+        return VNE_OK;
     }
 
     StepArgs step_args(const ServeTask &t, const DevTask &d, const GraphSet *set) const {
@@ -346,7 +390,13 @@ public:
 
     // One Lanczos step of every active slot.
     vne_status tick(const std::vector<ServeTask> &active, const std::vector<ServeQuery *> &qs) override {
+        VNE_TRY(flush_results());
         const int A = (int)active.size();
+        std::vector<int2> pmap, cmap;    // probe blocks and columns of the tasks started since the last tick
+        for (size_t i = 0; i < probes.size(); ++i) {
+            for (int b = 0; b < probes[i].n_blocks; ++b) pmap.push_back(make_int2((int)i, b));
+            for (int c = 0; c < probes[i].m_pad; ++c) cmap.push_back(make_int2((int)i, c));
+        }
         // descriptors: StepArgs[A], FinalizeArgs[A], then per tile width the
         // step and long-row maps (and per group size those of the group
         // slots), then the finalize map
@@ -436,6 +486,7 @@ public:
         }
         size_t bytes = rnd(sizeof(StepArgs) * A) + rnd(sizeof(FinalizeArgs) * A) + rnd(sizeof(int2) * fmap.size());
         bytes += rnd(sizeof(BoundArgs) * ba.size()) + rnd(sizeof(int2) * bmap.size()) + rnd(sizeof(StopArgs) * sta.size());
+        bytes += rnd(sizeof(ProbeArgs) * probes.size()) + rnd(sizeof(int2) * pmap.size()) + rnd(sizeof(int2) * cmap.size());
         for (auto &kv : smap) bytes += rnd(sizeof(int4) * kv.second.size());
         for (auto &kv : lmap) bytes += rnd(sizeof(int4) * kv.second.size());
         for (auto &kv : gmap) bytes += rnd(sizeof(int4) * kv.second.size());
@@ -480,9 +531,16 @@ public:
         const BoundArgs *d_ba = (const BoundArgs *)put(ba.data(), sizeof(BoundArgs) * ba.size());
         const int2 *d_bm = (const int2 *)put(bmap.data(), sizeof(int2) * bmap.size());
         const StopArgs *d_st = (const StopArgs *)put(sta.data(), sizeof(StopArgs) * sta.size());
+        const ProbeArgs *d_pa = (const ProbeArgs *)put(probes.data(), sizeof(ProbeArgs) * probes.size());
+        const int2 *d_pm = (const int2 *)put(pmap.data(), sizeof(int2) * pmap.size());
+        const int2 *d_cm = (const int2 *)put(cmap.data(), sizeof(int2) * cmap.size());
         VNE_TRY(hip_err(hipMemcpyAsync(d_desc, h, off, hipMemcpyHostToDevice, stream), "hipMemcpyAsync"));
         VNE_TRY(hip_err(hipEventRecord(ring_ev[r], stream), "hipEventRecord"));
         ring_used[r] = true;
+        if (!probes.empty())
+            VNE_TRY(hip_err(launch_probe_slots(d_pa, d_pm, (int32_t)pmap.size(), d_cm, (int32_t)cmap.size(), fp64, stream),
+                            "launch_probe_slots"));
+        probes.clear();
         // class 0 (the group slots when there are any, which carry most of
         // the work at saturation) on the tick's own stream, class i >= 1 on
         // side stream (i - 1) mod (the side streams this tick uses: at most
@@ -543,36 +601,24 @@ public:
         // cap before the record reaches the host: the device's count of the
         // steps taken is the one reported)
         const int64_t co = u.c_off;
-        return hip_err(launch_quadrature(d.alpha + co * t.k, d.beta + co * t.k, d.k_eff + co, d.norm2 + co, t.k,
-                                         steps, u.m, d_psi(q) + u.col0, d_flags(q), stream, fp64,
-                                         u.adaptive ? d.d_state + i : nullptr, u.uid, nullptr, d_steps(q)),
-                       "launch_quadrature");
+        if (quads.n == kQuadJobs) VNE_TRY(flush_results());
+        if (quads.n == 0) quads.first[0] = 0;
+        quads.job[quads.n] = QuadJob{d.alpha + co * t.k, d.beta + co * t.k, d.k_eff + co, d.norm2 + co,
+                                     d_psi(q) + u.col0, d_flags(q), u.adaptive ? d.d_state + i : nullptr, d_steps(q),
+                                     t.k, steps, u.m, u.uid};
+        quads.first[quads.n + 1] = quads.first[quads.n] + (u.m + 3) / 4;
+        quads.n++;
+        return VNE_OK;
     }
 
-    vne_status issue_stage(ServeQuery &q) override {
-        GpuQuery *x = gq(q);
-        VNE_TRY(hip_err(hipMemcpyAsync(x->h_buf, d_psi(q), (size_t)q.cols_issued * 8, hipMemcpyDeviceToHost, stream),
-                        "hipMemcpyAsync"));
-        VNE_TRY(hip_err(hipMemcpyAsync(x->h_buf + psi_cap + 1, d_flags(q), 4, hipMemcpyDeviceToHost, stream),
-                        "hipMemcpyAsync"));
-        return hip_err(hipEventRecord(x->ev, stream), "hipEventRecord");
-    }
+    vne_status issue_stage(ServeQuery &q) override { return issue_forms(q, q.cols_issued, psi_cap + 1, false); }
 
-    // estimator combine (eq. (3.8)) on the device and the copy of psi,
-    // estimate and flags to the host
-    vne_status issue_final(ServeQuery &q) override {
-        GpuQuery *x = gq(q);
-        VNE_TRY(hip_err(launch_combine(d_psi(q), q.N, 0, 0, d_est(q), stream), "launch_combine"));
-        VNE_TRY(hip_err(hipMemcpyAsync(x->h_buf, d_psi(q), (size_t)q.N * 8, hipMemcpyDeviceToHost, stream),
-                        "hipMemcpyAsync"));
-        VNE_TRY(hip_err(hipMemcpyAsync(x->h_buf + q.N, d_est(q), 8, hipMemcpyDeviceToHost, stream), "hipMemcpyAsync"));
-        // flags and the step count, adjacent words
-        VNE_TRY(hip_err(hipMemcpyAsync(x->h_buf + q.N + 1, d_flags(q), 8, hipMemcpyDeviceToHost, stream),
-                        "hipMemcpyAsync"));
-        return hip_err(hipEventRecord(x->ev, stream), "hipEventRecord");
-    }
+    // the estimator's mean (eq. (3.8)) too, behind the forms; flags and the
+    // step count are adjacent words
+    vne_status issue_final(ServeQuery &q) override { return issue_forms(q, q.N, q.N + 1, true); }
 
     vne_status ready(ServeQuery &q, bool block, bool *done) override {
+        VNE_TRY(flush_results());
         hipError_t e = hipEventQuery(gq(q)->ev);
         if (e == hipErrorNotReady && block) e = hipEventSynchronize(gq(q)->ev);
         *done = e == hipSuccess;
@@ -595,6 +641,7 @@ public:
     void close_query(ServeQuery &q) override {
         GpuQuery *x = gq(q);
         if (!x) return;
+        flush();
         if (x->h_buf) pinned_pool.push_back(x->h_buf);
         if (x->ev) event_pool.push_back(x->ev);
         delete x;
@@ -604,6 +651,7 @@ public:
     void release_graph(ServeQuery &q) override {
         GpuQuery *x = gq(q);
         if (!x || !x->g) return;
+        flush();
         std::lock_guard<std::recursive_mutex> lk(ctx->mu);
         x->g->in_use--;
         x->g = nullptr;
