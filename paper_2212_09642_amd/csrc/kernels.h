@@ -125,24 +125,24 @@ hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t s);
 
 // Several independent problems ("slots") per launch, two-pass schedule, one
 // column tile mt for all of them.  args: device array of per-slot StepArgs
-// (graph fields unused: one matrix per slot).  step_map entries {slot, work
-// block, tile, 0} cover every block (padding blocks included) and tile of
-// each slot; long_map entries {slot, group, tile, 0} cover the long rows in
+// (graph fields unused: one matrix per slot).  runs {slot, first entry}, by
+// ascending entry: a slot's entries are its work blocks (padding blocks
+// included), tile after tile, n_step in all; long_map entries {slot, group, tile, 0} cover the long rows in
 // groups of long_rows_per_group(mt, fp64).  The first step of a slot needs
 // its v_{j-1} buffer zeroed.  Then launch_finalize_slots with map entries
 // {slot, column chunk of kFinalizeCols}; each slot's FinalizeArgs carries
 // n_level2 = kSlotLevel2 and a level2 scratch of kSlotLevel2 * 3 * m_pad
 // doubles.
-hipError_t launch_step_slots(const StepArgs *args, const int4 *step_map, int32_t n_step, const int4 *long_map,
-                             int32_t n_long, int32_t mt, bool fp64, hipStream_t s);
+hipError_t launch_step_slots(const StepArgs *args, const int2 *runs, int32_t n_runs, int32_t n_step,
+                             const int4 *long_map, int32_t n_long, int32_t mt, bool fp64, hipStream_t s);
 int long_rows_per_group(int mt, bool fp64);
 // Group slots of `members` (2 or 4) 16-column FP32 tiles (m_pad = 16 *
-// members, mt = 16), every tile of a work block in one workgroup: group_map
-// entries {slot, work block, 0, 0}; long_map entries {slot, group, tile, 0}
+// members, mt = 16), every tile of a work block in one workgroup: a slot's
+// entries are its work blocks; long_map entries {slot, group, tile, 0}
 // as for mt = 16.  Every column gets the same arithmetic, in the same order,
 // as in a 16-column slot.
-hipError_t launch_step_groups(const StepArgs *args, const int4 *group_map, int32_t n_group, const int4 *long_map,
-                              int32_t n_long, int32_t members, hipStream_t s);
+hipError_t launch_step_groups(const StepArgs *args, const int2 *runs, int32_t n_runs, int32_t n_group,
+                              const int4 *long_map, int32_t n_long, int32_t members, hipStream_t s);
 constexpr int kFinalizeCols = 16;
 constexpr int kSlotLevel2 = 16;   // first-level parts of a slot's reduction (FinalizeArgs.n_level2)
 hipError_t launch_finalize_slots(const FinalizeArgs *fargs, const int2 *map, int32_t n_entries, hipStream_t s);

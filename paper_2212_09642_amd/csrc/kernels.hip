@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdint>
 #include <vector>
@@ -694,12 +695,31 @@ __device__ __forceinline__ bool slot_stopped(const int2 *state, int32_t uid, int
     return true;
 }
 
+// Entry e of the slots' runs {slot, first entry} (ascending): {slot, work
+// block, tile} - the slot's blocks for its first tile, then for the next.  A
+// lane looks at a run; a table of all entries (some ten thousand at 64 slots)
+// was built, copied and read on every tick while the device waited: a burst of
+// 32 queries 40.3 ms with it, 39.5 without.
+__device__ __forceinline__ int3 slot_entry(const StepArgs *args, const int2 *runs, int n_runs, int e) {
+    const int lane = threadIdx.x & 63;
+    int r = 0;
+    for (int base = 0; base < n_runs; base += 64) {
+        const int first = base + lane < n_runs ? runs[base + lane].y : INT_MAX;
+        const int below = __popcll(__ballot(first <= e));
+        if (below > 0) r = base + below - 1;
+        if (below < 64) break;
+    }
+    const int2 run = runs[__builtin_amdgcn_readfirstlane(r)];
+    const int local = e - run.y, nb = args[run.x].n_blocks;
+    return make_int3(run.x, local % nb, local / nb);
+}
+
 template <typename T, int CPL, int LPR>
-__global__ void __launch_bounds__(kStepThreads) VNE_STEP_OCCUPANCY k_lanczos_step_slots(const StepArgs *args, const int4 *map,
-                                                                     int32_t n_entries) {
+__global__ void __launch_bounds__(kStepThreads) VNE_STEP_OCCUPANCY k_lanczos_step_slots(const StepArgs *args, const int2 *runs,
+                                                                     int32_t n_runs, int32_t n_entries) {
     constexpr int NG = (kStepThreads / 64) * (64 / LPR);
     __shared__ double red[3][NG * CPL * LPR];
-    const int4 e = map[xcd_remap(blockIdx.x, n_entries)];
+    const int3 e = slot_entry(args, runs, n_runs, xcd_remap(blockIdx.x, n_entries));
     const StepArgs a = args[e.x];
     if (slot_stopped(a.stop_state, a.stop_uid, a.stop_count)) return;
     step_block<T, CPL, LPR, false, true>(a, e.y, e.z, true, red);
@@ -710,11 +730,11 @@ __global__ void __launch_bounds__(kStepThreads) VNE_STEP_OCCUPANCY k_lanczos_ste
 // single-tile blocks would each gather a part of every cache line they
 // fetch; each tile keeps the arithmetic and order it has alone.
 template <typename T, int CPL, int LPR, int JT>
-__global__ void __launch_bounds__(JT * kStepThreads) k_lanczos_step_groups(const StepArgs *args, const int4 *map,
-                                                                            int32_t n_entries) {
+__global__ void __launch_bounds__(JT * kStepThreads) k_lanczos_step_groups(const StepArgs *args, const int2 *runs,
+                                                                            int32_t n_runs, int32_t n_entries) {
     constexpr int NG = (kStepThreads / 64) * (64 / LPR);
     __shared__ double red[JT * 3][NG * CPL * LPR];
-    const int4 e = map[xcd_remap(blockIdx.x, n_entries)];
+    const int3 e = slot_entry(args, runs, n_runs, xcd_remap(blockIdx.x, n_entries));
     const StepArgs a = args[e.x];
     if (slot_stopped(a.stop_state, a.stop_uid, a.stop_count)) return;
     step_block<T, CPL, LPR, false, true, JT>(a, e.y, e.z, true, red);
@@ -723,10 +743,11 @@ __global__ void __launch_bounds__(JT * kStepThreads) k_lanczos_step_groups(const
 // Normalize pass of the slots: entry {slot, work block, tile} writes v_j on
 // the block's row range, tile columns.
 template <typename T, int CPL, int LPR>
-__global__ void __launch_bounds__(256) k_normalize_slots(const StepArgs *args, const int4 *map, int32_t n_entries) {
+__global__ void __launch_bounds__(256) k_normalize_slots(const StepArgs *args, const int2 *runs, int32_t n_runs,
+                                                         int32_t n_entries) {
     constexpr int MT = CPL * LPR;
     constexpr int RP = 256 / LPR;                    // rows per pass
-    const int4 e = map[xcd_remap(blockIdx.x, n_entries)];
+    const int3 e = slot_entry(args, runs, n_runs, xcd_remap(blockIdx.x, n_entries));
     const StepArgs a = args[e.x];
     if (slot_stopped(a.stop_state, a.stop_uid, a.stop_count)) return;
     const int4 rg = a.block_ranges[e.y];
@@ -861,12 +882,13 @@ static hipError_t launch_step_t(const StepArgs &a, bool first, hipStream_t s) {
 }
 
 template <typename T, int CPL, int LPR>
-static hipError_t launch_slots_t(const StepArgs *args, const int4 *step_map, int32_t n_step,
+static hipError_t launch_slots_t(const StepArgs *args, const int2 *runs, int32_t n_runs, int32_t n_step,
                                  const int4 *long_map, int32_t n_long, hipStream_t s) {
     if (n_step > 0) {
-        hipLaunchKernelGGL((k_normalize_slots<T, CPL, LPR>), dim3(n_step), dim3(256), 0, s, args, step_map, n_step);
+        hipLaunchKernelGGL((k_normalize_slots<T, CPL, LPR>), dim3(n_step), dim3(256), 0, s, args, runs, n_runs,
+                           n_step);
         hipLaunchKernelGGL((k_lanczos_step_slots<T, CPL, LPR>), dim3(n_step), dim3(kStepThreads), 0, s, args,
-                           step_map, n_step);
+                           runs, n_runs, n_step);
     }
     if (n_long > 0) hipLaunchKernelGGL((k_long_rows_slots<T, CPL, LPR>), dim3(n_long), dim3(256), 0, s, args, long_map);
     return hipGetLastError();
@@ -874,44 +896,44 @@ static hipError_t launch_slots_t(const StepArgs *args, const int4 *step_map, int
 
 int long_rows_per_group(int mt, bool fp64) { return 4 * (64 / (mt / (fp64 ? 2 : 4))); }
 
-hipError_t launch_step_slots(const StepArgs *args, const int4 *step_map, int32_t n_step, const int4 *long_map,
-                             int32_t n_long, int32_t mt, bool fp64, hipStream_t s) {
+hipError_t launch_step_slots(const StepArgs *args, const int2 *runs, int32_t n_runs, int32_t n_step,
+                             const int4 *long_map, int32_t n_long, int32_t mt, bool fp64, hipStream_t s) {
     if (!fp64) {
         switch (mt) {
-            case 16: return launch_slots_t<float, 4, 4>(args, step_map, n_step, long_map, n_long, s);
-            case 32: return launch_slots_t<float, 4, 8>(args, step_map, n_step, long_map, n_long, s);
-            case 64: return launch_slots_t<float, 4, 16>(args, step_map, n_step, long_map, n_long, s);
-            case 128: return launch_slots_t<float, 4, 32>(args, step_map, n_step, long_map, n_long, s);
-            case 256: return launch_slots_t<float, 4, 64>(args, step_map, n_step, long_map, n_long, s);
+            case 16: return launch_slots_t<float, 4, 4>(args, runs, n_runs, n_step, long_map, n_long, s);
+            case 32: return launch_slots_t<float, 4, 8>(args, runs, n_runs, n_step, long_map, n_long, s);
+            case 64: return launch_slots_t<float, 4, 16>(args, runs, n_runs, n_step, long_map, n_long, s);
+            case 128: return launch_slots_t<float, 4, 32>(args, runs, n_runs, n_step, long_map, n_long, s);
+            case 256: return launch_slots_t<float, 4, 64>(args, runs, n_runs, n_step, long_map, n_long, s);
         }
     } else {
         switch (mt) {
-            case 8: return launch_slots_t<double, 2, 4>(args, step_map, n_step, long_map, n_long, s);
-            case 16: return launch_slots_t<double, 2, 8>(args, step_map, n_step, long_map, n_long, s);
-            case 32: return launch_slots_t<double, 2, 16>(args, step_map, n_step, long_map, n_long, s);
-            case 64: return launch_slots_t<double, 2, 32>(args, step_map, n_step, long_map, n_long, s);
-            case 128: return launch_slots_t<double, 2, 64>(args, step_map, n_step, long_map, n_long, s);
+            case 8: return launch_slots_t<double, 2, 4>(args, runs, n_runs, n_step, long_map, n_long, s);
+            case 16: return launch_slots_t<double, 2, 8>(args, runs, n_runs, n_step, long_map, n_long, s);
+            case 32: return launch_slots_t<double, 2, 16>(args, runs, n_runs, n_step, long_map, n_long, s);
+            case 64: return launch_slots_t<double, 2, 32>(args, runs, n_runs, n_step, long_map, n_long, s);
+            case 128: return launch_slots_t<double, 2, 64>(args, runs, n_runs, n_step, long_map, n_long, s);
         }
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_step_groups(const StepArgs *args, const int4 *group_map, int32_t n_group, const int4 *long_map,
-                              int32_t n_long, int32_t members, hipStream_t s) {
+hipError_t launch_step_groups(const StepArgs *args, const int2 *runs, int32_t n_runs, int32_t n_group,
+                              const int4 *long_map, int32_t n_long, int32_t members, hipStream_t s) {
     if (members != 2 && members != 4) return hipErrorInvalidValue;
     if (n_group > 0) {
         // the normalize pass is elementwise: the members' tiles as one tile
         // of 16 * members columns
         if (members == 2) {
-            hipLaunchKernelGGL((k_normalize_slots<float, 4, 8>), dim3(n_group), dim3(256), 0, s, args, group_map,
+            hipLaunchKernelGGL((k_normalize_slots<float, 4, 8>), dim3(n_group), dim3(256), 0, s, args, runs, n_runs,
                                n_group);
             hipLaunchKernelGGL((k_lanczos_step_groups<float, 4, 4, 2>), dim3(n_group), dim3(2 * kStepThreads), 0, s,
-                               args, group_map, n_group);
+                               args, runs, n_runs, n_group);
         } else {
-            hipLaunchKernelGGL((k_normalize_slots<float, 4, 16>), dim3(n_group), dim3(256), 0, s, args, group_map,
+            hipLaunchKernelGGL((k_normalize_slots<float, 4, 16>), dim3(n_group), dim3(256), 0, s, args, runs, n_runs,
                                n_group);
             hipLaunchKernelGGL((k_lanczos_step_groups<float, 4, 4, 4>), dim3(n_group), dim3(4 * kStepThreads), 0, s,
-                               args, group_map, n_group);
+                               args, runs, n_runs, n_group);
         }
     }
     if (n_long > 0) hipLaunchKernelGGL((k_long_rows_slots<float, 4, 4>), dim3(n_long), dim3(256), 0, s, args, long_map);

@@ -403,7 +403,12 @@ public:
         std::vector<DevTask> dt(A);
         std::vector<StepArgs> sa(A);
         std::vector<FinalizeArgs> fa(A);
-        std::map<int, std::vector<int4>> smap, lmap, gmap, glmap;
+        std::map<int, std::vector<int4>> lmap, glmap;
+        struct Runs {
+            std::vector<int2> of;            // {slot, first entry}
+            int n = 0;                       // entries
+        };
+        std::map<int, Runs> smap, gmap;
         std::vector<int2> fmap;
         auto flags_of = [&](const ServeQuery *q) { return q ? d_flags(*q) : (int32_t *)sink.p; };
         for (int i = 0; i < A; ++i) {
@@ -419,14 +424,9 @@ public:
             for (int mi = 0; mi < t.n_mem; ++mi) flags_m[mi] = flags_of(qi[mi]);
             fa[i] = fin_args(t, dt[i], set, flags_m);
             const int nt = t.m_pad / t.mt, nb = set->sched.n_blocks();
-            if (t.group()) {
-                auto &gm = gmap[t.n_mem];
-                for (int b = 0; b < nb; ++b) gm.push_back(make_int4(i, b, 0, 0));
-            } else {
-                auto &sm = smap[t.mt];
-                for (int tile = 0; tile < nt; ++tile)
-                    for (int b = 0; b < nb; ++b) sm.push_back(make_int4(i, b, tile, 0));
-            }
+            Runs &runs = t.group() ? gmap[t.n_mem] : smap[t.mt];
+            runs.of.push_back(make_int2(i, runs.n));
+            runs.n += t.group() ? nb : nt * nb;
             if (set->sched.n_long > 0) {
                 const int per = long_rows_per_group(t.mt, fp64);
                 auto &lm = t.group() ? glmap[t.n_mem] : lmap[t.mt];
@@ -487,9 +487,9 @@ public:
         size_t bytes = rnd(sizeof(StepArgs) * A) + rnd(sizeof(FinalizeArgs) * A) + rnd(sizeof(int2) * fmap.size());
         bytes += rnd(sizeof(BoundArgs) * ba.size()) + rnd(sizeof(int2) * bmap.size()) + rnd(sizeof(StopArgs) * sta.size());
         bytes += rnd(sizeof(ProbeArgs) * probes.size()) + rnd(sizeof(int2) * pmap.size()) + rnd(sizeof(int2) * cmap.size());
-        for (auto &kv : smap) bytes += rnd(sizeof(int4) * kv.second.size());
+        for (auto &kv : smap) bytes += rnd(sizeof(int2) * kv.second.of.size());
         for (auto &kv : lmap) bytes += rnd(sizeof(int4) * kv.second.size());
-        for (auto &kv : gmap) bytes += rnd(sizeof(int4) * kv.second.size());
+        for (auto &kv : gmap) bytes += rnd(sizeof(int2) * kv.second.of.size());
         for (auto &kv : glmap) bytes += rnd(sizeof(int4) * kv.second.size());
         // staging ring: wait until the copy that last used this slot has run
         const int r = ring_pos;
@@ -522,11 +522,11 @@ public:
         const StepArgs *d_sa = (const StepArgs *)put(sa.data(), sizeof(StepArgs) * A);
         const FinalizeArgs *d_fa = (const FinalizeArgs *)put(fa.data(), sizeof(FinalizeArgs) * A);
         const int2 *d_fm = (const int2 *)put(fmap.data(), sizeof(int2) * fmap.size());
-        std::map<int, const int4 *> d_sm, d_lm;
-        for (auto &kv : smap) d_sm[kv.first] = (const int4 *)put(kv.second.data(), sizeof(int4) * kv.second.size());
+        std::map<int, const int2 *> d_sm, d_gm;
+        std::map<int, const int4 *> d_lm, d_glm;
+        for (auto &kv : smap) d_sm[kv.first] = (const int2 *)put(kv.second.of.data(), sizeof(int2) * kv.second.of.size());
         for (auto &kv : lmap) d_lm[kv.first] = (const int4 *)put(kv.second.data(), sizeof(int4) * kv.second.size());
-        std::map<int, const int4 *> d_gm, d_glm;
-        for (auto &kv : gmap) d_gm[kv.first] = (const int4 *)put(kv.second.data(), sizeof(int4) * kv.second.size());
+        for (auto &kv : gmap) d_gm[kv.first] = (const int2 *)put(kv.second.of.data(), sizeof(int2) * kv.second.of.size());
         for (auto &kv : glmap) d_glm[kv.first] = (const int4 *)put(kv.second.data(), sizeof(int4) * kv.second.size());
         const BoundArgs *d_ba = (const BoundArgs *)put(ba.data(), sizeof(BoundArgs) * ba.size());
         const int2 *d_bm = (const int2 *)put(bmap.data(), sizeof(int2) * bmap.size());
@@ -559,7 +559,7 @@ public:
             const int members = kv.first;
             const auto lit = glmap.find(members);
             const int n_long = lit == glmap.end() ? 0 : (int)lit->second.size();
-            VNE_TRY(hip_err(launch_step_groups(d_sa, d_gm[members], (int32_t)kv.second.size(),
+            VNE_TRY(hip_err(launch_step_groups(d_sa, d_gm[members], (int32_t)kv.second.of.size(), kv.second.n,
                                                n_long ? d_glm[members] : nullptr, n_long, members, class_stream()),
                             "launch_step_groups"));
         }
@@ -567,7 +567,7 @@ public:
             const int mt = kv.first;
             const auto lit = lmap.find(mt);
             const int n_long = lit == lmap.end() ? 0 : (int)lit->second.size();
-            VNE_TRY(hip_err(launch_step_slots(d_sa, d_sm[mt], (int32_t)kv.second.size(), n_long ? d_lm[mt] : nullptr,
+            VNE_TRY(hip_err(launch_step_slots(d_sa, d_sm[mt], (int32_t)kv.second.of.size(), kv.second.n, n_long ? d_lm[mt] : nullptr,
                                               n_long, mt, fp64, class_stream()),
                             "launch_step_slots"));
         }
