@@ -237,6 +237,7 @@ public:
     }
 
     vne_status flush_results() {
+        VNE_TRY(lost);
         if (quads.n > 0) VNE_TRY(hip_err(launch_quadrature_jobs(quads, fp64, stream), "launch_quadrature_jobs"));
         quads.n = 0;
         if (outs.n > 0) VNE_TRY(hip_err(launch_forms_jobs(outs, stream), "launch_forms_jobs"));
@@ -246,13 +247,16 @@ public:
         return VNE_OK;
     }
 
-    // before a query or its graph goes (an error is the next call's)
+    // before a query or its graph goes: what cannot be launched is dropped,
+    // and the next tick or look for a result returns the error
+    vne_status lost = VNE_OK;
     void flush() {
-        if (flush_results() != VNE_OK || flush_probes() != VNE_OK) {
-            quads.n = outs.n = 0;
-            out_events.clear();
-            probes.clear();
-        }
+        lost = flush_results();
+        if (lost == VNE_OK) lost = flush_probes();
+        if (lost == VNE_OK) return;
+        quads.n = outs.n = 0;
+        out_events.clear();
+        probes.clear();
     }
 
     // the query's next copy: nothing is ready before its event is recorded
