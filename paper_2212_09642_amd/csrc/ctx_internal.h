@@ -256,7 +256,10 @@ vne_status fetch_results(vne_ctx *c, Plan *p, ResultPart *parts, int n, int comb
 // formed too (-1: they are in p->estimate)
 vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne_result *out, Plan *extra,
                     int combine_kind);
-constexpr size_t kCollectBytes = 1 << 20;
+// Largest results written by one kernel; larger ones go by copies, which take
+// the copy engines (an estimate's coefficients, one launch against copies: 2
+// MB 155 and 223 us, 4 MB 289 and 386, 8 MB 776 and 649).
+constexpr size_t kCollectBytes = 4 << 20;
 
 // On-chip runs (resident_run.hip): whole Lanczos loops inside workgroups.
 // The layout of one graph's on-chip run and its columns per workgroup, or

@@ -903,7 +903,7 @@ vne_status fetch_results(vne_ctx *c, Plan *p, ResultPart *parts, int n, int comb
         parts[q].at = at;
         at += (parts[q].bytes + 7) / 8 * 8;
     }
-    // one launch up to the size at which copies take the copy engines
+    // one launch, or copies for large results
     if (need <= kCollectBytes) {
         CollectArgs a{};
         auto part = [&](void *dst, const void *src, size_t bytes) {

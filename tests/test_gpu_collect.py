@@ -1,5 +1,5 @@
 """Results of a call through one launch into pinned memory, and through copies
-past 1 MiB: the arrays that both calls return are equal bit for bit (the second
+past 4 MiB: the arrays that both calls return are equal bit for bit (the second
 call asks for the coefficients as well, which takes it past the size), and the
 estimate is the mean of the forms, whose sum the two sides order differently
 (n eps relative, 1e-13)."""
@@ -13,9 +13,9 @@ from gpu_common import ctx, _say, _setup  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# m * 100 steps * 16 bytes of coefficients: below, just below and past 1 MiB
-@pytest.mark.parametrize("m", [1, 640, 700])
-@pytest.mark.parametrize("n", [900, 70000])
+# m * 100 steps * 16 bytes of coefficients: below, just below and past 4 MiB
+@pytest.mark.parametrize("m", [1, 2500, 2700])
+@pytest.mark.parametrize("n", [900, 42000])
 def test_small_and_large_results(ctx, n, m):
     _say("case results n=%d m=%d" % (n, m))
     nn, e = synth.watts_strogatz(n, 4, 0.1, 3)
