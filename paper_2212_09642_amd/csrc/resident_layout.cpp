@@ -7,7 +7,7 @@
 namespace vne {
 
 bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
-                           int32_t max_rounds, ResidentLayout *out) {
+                           int32_t max_rounds, ResidentLayout *out, bool fp64) {
     if (n < 1 || waves < 1 || waves > 16 || n > (int64_t)waves * max_rounds * 64) return false;
     ResidentLayout L;
     L.waves = waves;
@@ -46,6 +46,10 @@ bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const dou
     const int64_t n_short = (n - n_long + 63) / 64;
     L.rounds = (int32_t)((n_long > 0 ? 1 : 0) + (n_short + waves - 1) / waves);
     if (L.rounds > max_rounds || L.positions() > kResidentMaxPositions) return false;
+    int64_t word_rows = kResidentSpareRows;
+    for (int64_t q = 0; q < n_long; ++q) word_rows += (len[order[q]] + 127) / 128;
+    for (int64_t a = n_long; a < n; a += 64) word_rows += (len[order[a]] + 3) / 4 * 2;
+    if (word_rows > resident_max_word_rows(L.unit, fp64)) return false;
     // slices to waves: long rows in turn, then the short slices, longest
     // first, to the wave with the least work that has room
     std::vector<std::vector<std::pair<int64_t, int64_t>>> of_wave(waves);   // {first in order, rows}, -1 - w: long

@@ -45,9 +45,17 @@ constexpr int32_t kResidentSpareRows = 8;
 // Most positions (they and the zero fit 16 bits).
 constexpr int32_t kResidentMaxPositions = 65472;
 
-// Layout for `waves` wavefronts (1 .. 16).  Returns false when the rows need
-// more than max_rounds rounds.
+// Most word rows, spare ones included: the kernel's byte offsets into the
+// words (256 bytes a row) and the values (64 pairs a row) are 32-bit.  FP32
+// matrices of unequal values reach it at about 1.07e9 entries.
+constexpr int64_t resident_max_word_rows(bool unit, bool fp64) {
+    return (int64_t(1) << 32) / (unit ? 256 : fp64 ? 64 * 16 : 64 * 8);
+}
+
+// Layout for `waves` wavefronts (1 .. 16) and vectors of the given type.
+// Returns false when the rows need more than max_rounds rounds, or more word
+// rows than resident_max_word_rows.
 bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
-                           int32_t max_rounds, ResidentLayout *out);
+                           int32_t max_rounds, ResidentLayout *out, bool fp64 = true);
 
 }  // namespace vne

@@ -47,7 +47,8 @@ DevLayout *layout_of(vne_ctx *c, int32_t gid, int waves, bool fp64) {
     auto &slot = g->layouts[key];
     ResidentLayout h;
     const int most = fp64 ? kResidentSlots64 : kResidentSlots32;
-    if (!build_resident_layout(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves, most, &h))
+    if (!build_resident_layout(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves, most, &h,
+                               fp64))
         return nullptr;
     if (resident_lds(h.positions(), 1, fp64) > kResidentLds) return nullptr;
     auto d = std::make_unique<DevLayout>();
