@@ -87,6 +87,66 @@ static void ranges_from_items(Schedule &s) {
     }
 }
 
+static void front_costs(Schedule &s) {
+    s.most_segs = 0;
+    s.long_entries = 0;
+    auto entries_of = [&](int32_t L) -> int64_t {
+        return s.segs[s.long_first[L] + s.long_nseg[L] - 1].p1 - s.segs[s.long_first[L]].p0;
+    };
+    for (int32_t L = 0; L < s.n_long; ++L) {
+        s.most_segs = std::max(s.most_segs, s.long_nseg[L]);
+        s.long_entries += entries_of(L);
+    }
+    for (int i = 0; i < kLaneClasses; ++i) {
+        const int per = long_rows_per_block(1 << i);
+        const double groups = 256 >> i;        // lane groups of a block of 256 threads
+        double most = 0.0, idle = 0.0;
+        for (int32_t L0 = 0; L0 < s.n_long; L0 += per) {
+            int64_t entries = 0;
+            for (int32_t L = L0; L < std::min(L0 + per, s.n_long); ++L) entries += entries_of(L);
+            const double rounds = (double)entries / (64.0 * groups);
+            most = std::max(most, std::max(1.0, rounds));
+            idle += std::max(0.0, 1.0 - rounds);
+        }
+        s.front[i].most = (float)most;
+        s.front[i].idle = (float)idle;
+    }
+}
+
+bool long_rows_first(const Schedule &s, int64_t nnz, int m_pad, int mt, bool fp64) {
+    if (s.n_long == 0) return false;
+    // Front blocks save a launch and its chain of sums (5 to 10 us a step, and
+    // the XCD that holds the segments is not behind the others).  They lose,
+    // by the same and by far more, where (us a step, launch / front)
+    //  - a block of hubs is a longer chain than the rest of the step: its
+    //    rounds at 6 to 15 us each, then a row's segments added by one lane
+    //    group (one row of 1e5 entries in n = 2e5, 16 columns 104 / 202, 64
+    //    columns 169 / 618; star of 2e5 rows, 16 columns 177 / 425);
+    //  - long rows hold much of the matrix: the ordinary blocks have less to
+    //    do, and a block of a row of 65 to some hundred entries keeps most of
+    //    its lane groups idle in a workgroup's place (ER of average degree
+    //    100, n = 5e4, 16 columns 268 / 322, 64 columns 666 / 1085; BA m = 20,
+    //    n = 5e4, 64 columns 146 / 181, m = 10, 82 / 87, m = 8, 78 / 67; in
+    //    narrow FP32 tiles, four or two rows a block, later: m = 10, 16
+    //    columns 54 / 45), sooner where they are little more than a segment
+    //    (ER of average degree 50, 64 columns 108 / 120), or where they are
+    //    many beside the step's time.
+    const int es = fp64 ? 8 : 4, lanes = mt / (fp64 ? 2 : mt % 3 == 0 ? 3 : 4), tiles = m_pad / mt;
+    int i = 0;
+    while (i + 1 < kLaneClasses && (2 << i) <= lanes) ++i;
+    const bool narrow = !fp64 && lanes <= 8;
+    const double share = (double)(s.long_entries + 4 * (int64_t)s.n_seg) / (double)(nnz + 4 * s.n_rows);
+    const double mean = (double)s.long_entries / s.n_long;
+    if (share > (mean < 96.0 ? 0.02 : narrow ? 0.25 : 0.17)) return false;
+    // the step by its bytes at 6.5 TB/s (six streams of the block; per tile
+    // the matrix and a gather of at least a line per entry) and its launches
+    const double step_us = 15.0 + (6.0 * (double)s.n_rows * m_pad * es +
+                                   (double)tiles * (double)nnz * (4.0 + es + std::max(mt * es, 128))) / 6.5e6;
+    const double round_us = lanes <= 2 ? 15.0 : fp64 ? (lanes <= 8 ? 9.0 : 5.6) : (lanes <= 8 ? 8.0 : 6.6);
+    const double chain_us = round_us * s.front[i].most + 0.05 * s.most_segs;
+    return chain_us < std::max(round_us + 3.0, 0.45 * step_us) && tiles * s.front[i].idle < 16.0 * step_us;
+}
+
 Schedule build_schedule(const int32_t *row_ptr, int64_t n, int32_t seg_len, int64_t cost_per_block,
                         int32_t max_blocks, bool pad8) {
     Schedule s;
@@ -134,6 +194,7 @@ Schedule build_schedule(const int32_t *row_ptr, int64_t n, int32_t seg_len, int6
     while (b < nb) s.block_begin[b++] = (int32_t)n_items;
     s.block_begin[nb] = (int32_t)n_items;
     ranges_from_items(s);
+    front_costs(s);
     return s;
 }
 
@@ -175,6 +236,7 @@ Schedule stack_schedules(const std::vector<Schedule> &parts, const std::vector<i
         for (int q = 0; q < 4; ++q) s.block_ranges.push_back(0);
         block_graph->push_back(G ? (int32_t)G - 1 : 0);
     }
+    front_costs(s);
     return s;
 }
 

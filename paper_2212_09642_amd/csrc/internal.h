@@ -27,6 +27,18 @@ struct SegItem {
 // Blocks take contiguous item ranges of roughly equal cost; block_ranges
 // holds, per block, its segment range and its row range:
 // {seg_begin, seg_end, row_begin, row_end}.
+//
+// Long rows may run in blocks of their own at the front of the step's grid
+// (long_rows_per_block of them each).  What such blocks cost, per number of
+// lanes that a row's lane group has (2^i lanes in entry i), in rounds of 64
+// entries a lane group:
+struct FrontCost {
+    float most = 0.0f;      // the block with the most work
+    float idle = 0.0f;      // sum over the blocks of what they lack of a full round
+};
+constexpr int kLaneClasses = 7;           // 1 .. 64 lanes
+constexpr int long_rows_per_block(int lanes) { return lanes <= 4 ? 4 : lanes == 8 ? 2 : 1; }
+
 struct Schedule {
     int32_t seg_len = 0;
     int32_t n_seg = 0;                    // segment items
@@ -36,6 +48,9 @@ struct Schedule {
     std::vector<int32_t> long_nseg;       // [n_long]
     std::vector<int32_t> block_begin;     // [n_blocks + 1] item ranges
     std::vector<int32_t> block_ranges;    // [4 * n_blocks]
+    int32_t most_segs = 0;                // of one long row
+    int64_t long_entries = 0;             // entries of the long rows
+    FrontCost front[kLaneClasses];
     int64_t n_items() const { return (int64_t)n_seg + n_rows; }
     int64_t n_rows = 0;
     int32_t n_blocks() const { return (int32_t)block_ranges.size() / 4; }
@@ -53,6 +68,10 @@ Schedule build_schedule(const int32_t *row_ptr, int64_t n, int32_t seg_len,
 Schedule stack_schedules(const std::vector<Schedule> &parts, const std::vector<int64_t> &row_offset,
                          const std::vector<int64_t> &nnz_offset, std::vector<int32_t> *graph_block_begin,
                          std::vector<int32_t> *graph_long_begin, std::vector<int32_t> *block_graph);
+
+// Whether the long rows of a step over m_pad columns in tiles of mt run at the
+// front of its grid (the results are the same bits either way).
+bool long_rows_first(const Schedule &s, int64_t nnz, int m_pad, int mt, bool fp64);
 
 // Validation shared by vne_csr_validate and vne_graph_register (host arrays).
 vne_status validate_host_csr(const vne_csr *csr, uint32_t flags, std::string *msg);

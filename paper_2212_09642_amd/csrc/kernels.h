@@ -42,6 +42,7 @@ struct StepArgs {
     int32_t n_blocks;
     double *seg_acc;            // [n_seg][m_pad]
     int32_t n_long;             // rows split into segments
+    int32_t long_front;         // launch_step: long rows at the front of the grid (long_rows_first)
     const int32_t *long_first;
     const int32_t *long_nseg;
     double *long_part;          // [n_long][3][m_pad]
@@ -119,7 +120,7 @@ int pad_columns(int m, int mt);
 // padding, CSR passes and gathers move the fewest bytes per step.
 int choose_plan_tile(int m, bool fp64, int64_t n, int64_t nnz);
 
-// [normalize pass,] step kernel, then (if the matrix has long rows) the long-row kernel
+// [normalize pass,] step kernel, then (long rows, not at its front) the long-row kernel
 hipError_t launch_step(const StepArgs &a, bool fp64, bool first, hipStream_t s);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t s);
 

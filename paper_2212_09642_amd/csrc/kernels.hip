@@ -544,8 +544,8 @@ __device__ __forceinline__ void step_block(const StepArgs &a, int b, int tile0, 
                     my2[k] += dvv[k];
                 }
             } else {
-                // segment of a long row: its partial product is finished by
-                // k_long_rows_slots after this kernel (the boundary orders it)
+                // segment of a long row: its partial product is finished by the long-row
+                // kernel after this one (the boundary orders it)
                 double *dst = a.seg_acc + (int64_t)cur.it * core.ld + core.c0;
 #pragma unroll
                 for (int k = 0; k < CPL; ++k) dst[k] = acc[k];
@@ -613,7 +613,7 @@ __device__ __forceinline__ void finish_long_row(const StepArgs &a, int L,
     }
 }
 
-// The long rows of block b, long_rows<LPR>() of them: their segments
+// The long rows of block b, long_rows_per_block(LPR) of them: their segments
 // (contiguous in segs) over the block's lane groups, then a lane group a row
 // adds and finishes.  A launch of its own for the second part was 5.5 to 8 us
 // a step, a tenth of a step of 5e4 rows; here it runs beside the other rows,
@@ -623,16 +623,13 @@ __device__ __forceinline__ void finish_long_row(const StepArgs &a, int L,
 // preferential-attachment graph are its largest and are neighbours) would
 // outlast the step (BA n = 5e4, 64 columns, us a step: 43.9 with the
 // launch, 50.6 with four rows a block, 39.5 with one; BA n = 2e5, 16 columns
-// 56.1 and 48.2 with four).
-template <int LPR>
-constexpr int long_rows() { return LPR <= 4 ? 4 : LPR == 8 ? 2 : 1; }
-
+// 56.1 and 48.2 with four).  Where they pay: long_rows_first.
 template <typename T, int CPL, int LPR, bool FIRST, bool TWO>
 __device__ __forceinline__ void long_block(const StepArgs &a, int b, int tile) {
     using Core = StepCore<T, CPL, LPR, FIRST, TWO>;
     constexpr int GPW = 64 / LPR;
     constexpr int NG = (kStepThreads / 64) * GPW;
-    constexpr int kRows = long_rows<LPR>();
+    constexpr int kRows = long_rows_per_block(LPR);
     static_assert(NG >= kRows, "a lane group per row");
     const int lane = threadIdx.x & 63;
     const int gid = (threadIdx.x >> 6) * GPW + lane / LPR, gl = lane % LPR;
@@ -858,8 +855,9 @@ static void launch_step_k(const StepArgs &a, hipStream_t s) {
     }
     // blocks of long rows at the front, unless rows of several graphs would
     // meet in one (the lazy schedule needs its graph's scalars throughout)
-    const bool front = a.n_long > 0 && (TWO || !a.block_graph);
-    const int n_front = front ? ((a.n_long + long_rows<LPR>() - 1) / long_rows<LPR>() + 7) / 8 * 8 : 0;
+    const bool front = a.n_long > 0 && a.long_front && (TWO || !a.block_graph);
+    constexpr int kRows = long_rows_per_block(LPR);
+    const int n_front = front ? ((a.n_long + kRows - 1) / kRows + 7) / 8 * 8 : 0;
     dim3 grid(n_front + a.n_blocks, a.n_tiles);
     hipLaunchKernelGGL((k_lanczos_step<T, CPL, LPR, FIRST, TWO>), grid, dim3(kStepThreads), 0, s, a);
     if (a.n_long > 0 && !front) {

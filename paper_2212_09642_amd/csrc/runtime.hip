@@ -486,6 +486,7 @@ vne_status run_lanczos(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, 
     a.n_blocks = s.n_blocks();
     a.seg_acc = (double *)p->seg_acc.p;
     a.n_long = s.n_long;
+    a.long_front = long_rows_first(s, set->nnz, p->m_pad, mt, p->fp64) ? 1 : 0;
     a.long_first = (const int32_t *)set->long_first.p;
     a.long_nseg = (const int32_t *)set->long_nseg.p;
     a.long_part = (double *)p->long_part.p;
