@@ -216,12 +216,13 @@ vne_status vne_graph_release(vne_ctx *ctx, int32_t graph_id);
  * tiles, its tiles run as up to two concurrent chains, each chain's step
  * loop on a stream the context owns (VNE_CHAINS, default 2, 1 disables); the
  * context's stream waits for them, and the results are bitwise those of one
- * chain.  RADEMACHER, COLORING and DENSE estimates of a matrix small enough
- * for a column of its Lanczos vector to fit in a CU's LDS (about 39 000 rows
- * in FP32, 19 000 in FP64) run whole columns inside workgroups instead, where
- * that is faster by a rule on sizes (VNE_RESIDENT: 0 never, 1 wherever the
- * rows fit); VNE_TILE, VNE_SCHED and VNE_AUTOTUNE=0 keep the launched steps.
- * Only the order of the FP64 sums differs. */
+ * chain.  On a context with no HBM budget, RADEMACHER, COLORING and DENSE
+ * estimates of a matrix small enough for a column of its Lanczos vector to fit
+ * in a CU's LDS (about 39 000 rows in FP32, 19 000 in FP64) run whole columns
+ * inside workgroups instead, where that is faster by a rule on sizes
+ * (VNE_RESIDENT: 0 never, 1 wherever the rows fit); VNE_TILE, VNE_SCHED and
+ * VNE_AUTOTUNE=0 keep the launched steps.  Only the order of the FP64 sums
+ * differs. */
 vne_status vne_entropy_estimate(vne_ctx *ctx, int32_t graph_id, const vne_probes *probes,
                                 int32_t k_steps, uint32_t mode, vne_result *out);
 

@@ -136,7 +136,9 @@ vne_status upload_widths(vne_ctx *c, Plan *p) {
 
 DevLayout *chip_choice(vne_ctx *c, GraphSet *set, const Plan *p, int *cols) {
     const int mode = chip_mode();
-    if (mode == 0 || set->G != 1 || set->n > lds_elements(p->fp64)) return nullptr;
+    // (with a memory budget the launched steps, whose allocations do not
+    // depend on the matrix's size or the rule)
+    if (mode == 0 || c->budget != 0 || set->G != 1 || set->n > lds_elements(p->fp64)) return nullptr;
     const int waves = (int)std::min<int64_t>(16, (set->n + 63) / 64);
     // one column per workgroup while a CU each is left, then as many as fit
     const int es = p->fp64 ? 8 : 4;

@@ -1,0 +1,39 @@
+"""Limits of the on-chip runs: contexts with a memory budget keep the launched
+steps and their allocations."""
+import numpy as np
+import pytest
+
+import synth
+import paper_2212_09642_amd as vne
+from gpu_common import _say
+
+pytestmark = pytest.mark.gpu
+
+
+def _register(c, n, e, fp64=False):
+    g = vne.laplacian_from_edges(n, e, np.float64 if fp64 else np.float32)
+    return c.register(g["row_ptr"], g["col_idx"], g["values"], g["scale"], node_keys=g["node_ids"])
+
+
+@pytest.mark.parametrize("fp64", [False, True])
+def test_budget_keeps_the_launched_allocations(fp64, monkeypatch):
+    mode = vne.MODE_DESING | (vne.MODE_F64 if fp64 else 0)
+
+    def used(budget):
+        """Bytes after registration and after each of three calls."""
+        with vne.Context(0, hbm_budget_bytes=budget) as c:
+            gid = _register(c, *synth.erdos_renyi(3000, 8.0, 5), fp64)
+            out = [c.memory()]
+            for m in (16, 300):
+                c.estimate(gid, vne.PROBE_RADEMACHER, m, 8, mode, seed=1)
+                out.append(c.memory())
+            c.estimate_batch([dict(gid=gid, kind=vne.PROBE_RADEMACHER, m=8, k=8, seed=1)], mode)
+            return out + [c.memory()]
+
+    _say("case budget fp64=%s" % fp64)
+    monkeypatch.setenv("VNE_RESIDENT", "0")
+    want = used(0)
+    monkeypatch.delenv("VNE_RESIDENT")
+    assert used(1 << 30) == want
+    # what just fits without the chip fits
+    assert used(want[-1]) == want
