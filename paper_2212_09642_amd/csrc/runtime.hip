@@ -39,6 +39,10 @@ vne_status fail(vne_ctx *c, vne_status st, const std::string &m) {
 
 vne_status hip_fail(vne_ctx *c, hipError_t e, const char *what) {
     c->err = std::string(what) + ": " + hipGetErrorString(e);
+    // reported here: the next launch's check is not to find it again (a call
+    // after a failed allocation, or the launched steps where a layout of the
+    // on-chip ones found no room)
+    (void)hipGetLastError();
     return e == hipErrorOutOfMemory ? VNE_ENOMEM : VNE_EDEVICE;
 }
 

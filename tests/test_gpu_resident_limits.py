@@ -1,5 +1,6 @@
 """Limits of the on-chip runs: contexts with a memory budget keep the launched
-steps and their allocations."""
+steps and their allocations; a failed allocation leaves no error for the
+launches after it."""
 import numpy as np
 import pytest
 
@@ -37,3 +38,16 @@ def test_budget_keeps_the_launched_allocations(fp64, monkeypatch):
     assert used(1 << 30) == want
     # what just fits without the chip fits
     assert used(want[-1]) == want
+
+
+def test_failed_allocation_is_reported_once():
+    _say("case call after a failed allocation")
+    with vne.Context(0) as c:
+        gid = _register(c, *synth.watts_strogatz(50000, 6, 0.1, 3))
+        before = c.estimate(gid, vne.PROBE_RADEMACHER, 8, 4, vne.MODE_DESING, seed=1)
+        held = c.memory()
+        with pytest.raises(vne.VneError) as ei:      # blocks of 420 GB each
+            c.estimate(gid, vne.PROBE_RADEMACHER, 1 << 20, 4, vne.MODE_DESING | vne.MODE_F64, want_coeffs=False)
+        assert ei.value.status == -2 and c.memory() == held
+        after = c.estimate(gid, vne.PROBE_RADEMACHER, 8, 4, vne.MODE_DESING, seed=1)
+        assert np.array_equal(before["quad"], after["quad"])
