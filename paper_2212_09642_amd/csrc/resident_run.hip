@@ -153,11 +153,14 @@ DevLayout *chip_choice(vne_ctx *c, GraphSet *set, const Plan *p, int *cols) {
     // 14.7 / 3.5; BA n = 12000, 300 columns 74 / 26; WS n = 12000, 21 columns
     // FP64 19.8 / 15.1; BA n = 36000, 64 columns 44 / 47; ER n = 39000, 8
     // columns 22 / 46.
+    // (the sizes alone decide, never a tile that was tuned: every call of a
+    // shape runs the same way)
+    const int mt = choose_plan_tile(p->m, p->fp64, set->n, set->nnz), m_pad = pad_columns(p->m, mt);
     auto slower = [&](double gathers, int columns) {
         const double rounds = std::ceil(std::ceil((double)p->m / columns) / 256.0);
         const double chip = rounds * (1.5 + gathers * (columns * es > 8 ? 30.0 : 20.0) / 2400.0);
-        const double bytes = 6.0 * (double)set->n * p->m_pad * es +
-                             (double)(p->m_pad / p->mt) * (double)set->nnz * (4.0 + es + std::max(p->mt * es, 128));
+        const double bytes = 6.0 * (double)set->n * m_pad * es +
+                             (double)(m_pad / mt) * (double)set->nnz * (4.0 + es + std::max(mt * es, 128));
         return mode != 1 && chip > 15.0 + bytes / 6.5e6;
     };
     // (no layout is built where even full slices would be slower)

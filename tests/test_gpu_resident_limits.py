@@ -1,6 +1,7 @@
 """Limits of the on-chip runs: contexts with a memory budget keep the launched
 steps and their allocations; a failed allocation leaves no error for the
-launches after it."""
+launches after it; whether a lone estimate runs on the chip depends on sizes
+alone."""
 import numpy as np
 import pytest
 
@@ -51,3 +52,31 @@ def test_failed_allocation_is_reported_once():
         assert ei.value.status == -2 and c.memory() == held
         after = c.estimate(gid, vne.PROBE_RADEMACHER, 8, 4, vne.MODE_DESING, seed=1)
         assert np.array_equal(before["quad"], after["quad"])
+
+
+def test_choice_does_not_depend_on_a_tuned_tile(tmp_path, monkeypatch):
+    """A graph near the line between the two ways, with the tuner's choice
+    fixed in its cache file at each tile in turn: every call runs the same
+    way as the first, and a repeated call gives the same bits."""
+    _say("case tuned tiles near the rule's line")
+    cache = tmp_path / "tiles"
+    monkeypatch.setenv("VNE_AUTOTUNE_CACHE", str(cache))
+    n, e = synth.erdos_renyi(16500, 8.0, 5)
+    ways = set()
+    for tile in (None, 16, 32, 64):
+        if tile is not None:
+            lines = cache.read_text().split() if cache.exists() else []
+            if not lines:
+                break                        # every width went on the chip
+            cache.write_text("".join("%s %d\n" % (sig, tile) for sig in lines[::2]))
+        with vne.Context(0) as c:
+            gid = _register(c, n, e)
+            for m in (24, 32, 40, 48, 64, 80, 96):
+                got = []
+                for _ in range(3):
+                    out = c.estimate(gid, vne.PROBE_RADEMACHER, m, 6, vne.MODE_DESING, seed=2)
+                    got.append((c.last_plan(), out["quad"]))
+                assert got[0][0] == got[1][0] == got[2][0], (tile, m, got)
+                assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][1], got[2][1])
+                ways.add((m, got[0][0]["tile"] == 1))
+    assert len(ways) == 7, ways
