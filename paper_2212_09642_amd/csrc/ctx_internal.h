@@ -71,6 +71,7 @@ struct DevLayout {
     bool unit = false;
     double off_value = 0.0;
     int64_t gathers = 0;
+    bool there = false;              // its arrays are on the device
     DevBuf slices, words, vals, spans, row_of, diag;
 };
 
@@ -90,8 +91,8 @@ struct Graph {
     double fro2 = 0.0;                       // ||A||_F^2 = tr(A^2) for symmetric A
     double trace = 0.0;
     int in_use = 0;                          // queries of a running server on this graph
-    // on-chip layouts by (waves, FP64), built on first use; null: the rows do
-    // not fit (or the device had no room)
+    // on-chip layouts by (waves, FP64); null: the rows do not fit.  Their arrays
+    // go to the device for the first run that takes them.
     std::map<std::pair<int, int>, std::unique_ptr<DevLayout>> layouts;
 };
 

@@ -38,7 +38,13 @@ bool put(vne_ctx *c, DevBuf *b, const std::vector<T> &h) {
     return h.empty() || hipMemcpy(b->p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
 }
 
-// The layout of graph gid for a workgroup of `waves`; null: does not fit.
+bool build(const Graph *g, int waves, bool fp64, ResidentLayout *h) {
+    return build_resident_layout(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves,
+                                 fp64 ? kResidentSlots64 : kResidentSlots32, h, fp64);
+}
+
+// The layout of graph gid for a workgroup of `waves`, without its arrays; null:
+// does not fit.
 DevLayout *layout_of(vne_ctx *c, int32_t gid, int waves, bool fp64) {
     Graph *g = get_graph(c, gid);
     const auto key = std::make_pair(waves, (int)fp64);
@@ -46,10 +52,7 @@ DevLayout *layout_of(vne_ctx *c, int32_t gid, int waves, bool fp64) {
     if (it != g->layouts.end()) return it->second.get();
     auto &slot = g->layouts[key];
     ResidentLayout h;
-    const int most = fp64 ? kResidentSlots64 : kResidentSlots32;
-    if (!build_resident_layout(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves, most, &h,
-                               fp64))
-        return nullptr;
+    if (!build(g, waves, fp64, &h)) return nullptr;
     if (resident_lds(h.positions(), 1, fp64) > kResidentLds) return nullptr;
     auto d = std::make_unique<DevLayout>();
     d->waves = waves;
@@ -58,20 +61,26 @@ DevLayout *layout_of(vne_ctx *c, int32_t gid, int waves, bool fp64) {
     d->unit = h.unit;
     d->off_value = h.off_value;
     d->gathers = h.gathers;
+    slot = std::move(d);
+    return slot.get();
+}
+
+// Its arrays to the device; false: no room (the launched steps run, and a later
+// call may try again).
+bool bring(vne_ctx *c, int32_t gid, DevLayout *d, bool fp64) {
+    if (d->there) return true;
+    ResidentLayout h;
+    if (!build(get_graph(c, gid), d->waves, fp64, &h)) return false;
     const std::string err = c->err;
     bool ok = put(c, &d->slices, h.slices) && put(c, &d->words, h.words) && put(c, &d->spans, h.spans) &&
               put(c, &d->row_of, h.row_of) && put(c, &d->diag, h.diag);
     if (ok && !h.unit)
         ok = fp64 ? put(c, &d->vals, h.vals) : put(c, &d->vals, std::vector<float>(h.vals.begin(), h.vals.end()));
     if (!ok) {
-        // no room: the launched steps run, and a later call may try again
         for (DevBuf *b : {&d->slices, &d->words, &d->vals, &d->spans, &d->row_of, &d->diag}) dev_free(c, b);
-        g->layouts.erase(key);
         c->err = err;
-        return nullptr;
     }
-    slot = std::move(d);
-    return slot.get();
+    return d->there = ok;
 }
 
 // the widest column group (at most cap) that the layout has room for
@@ -168,14 +177,14 @@ DevLayout *chip_choice(vne_ctx *c, GraphSet *set, const Plan *p, int *cols) {
     DevLayout *L = layout_of(c, set->ids[0], waves, p->fp64);
     if (!L) return nullptr;
     *cols = widest(L, p->fp64, cap);
-    return slower((double)L->gathers, *cols) ? nullptr : L;
+    return !slower((double)L->gathers, *cols) && bring(c, set->ids[0], L, p->fp64) ? L : nullptr;
 }
 
 DevLayout *chip_layout(vne_ctx *c, int32_t gid, int max_rounds) {
     const Graph *g = get_graph(c, gid);
     if (chip_mode() == 0 || c->budget != 0 || g->n > (int64_t)1024 * max_rounds) return nullptr;
     DevLayout *L = layout_of(c, gid, (int)std::min<int64_t>(16, (g->n + 63) / 64), true);
-    return L && L->rounds <= max_rounds ? L : nullptr;
+    return L && L->rounds <= max_rounds && bring(c, gid, L, true) ? L : nullptr;
 }
 
 vne_status run_chip(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, bool desing, const DevLayout *L,
@@ -450,7 +459,7 @@ vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_
                 }
                 if (L) break;
             }
-            if (L) {
+            if (L && bring(c, ids[q], L, fp64)) {
                 small.push_back(q);
                 b.layout.push_back(L);
                 b.cols.push_back(cols);

@@ -1,7 +1,7 @@
 """Limits of the on-chip runs: contexts with a memory budget keep the launched
 steps and their allocations; a failed allocation leaves no error for the
 launches after it; whether a lone estimate runs on the chip depends on sizes
-alone."""
+alone, and one that does not holds no layout."""
 import numpy as np
 import pytest
 
@@ -80,3 +80,25 @@ def test_choice_does_not_depend_on_a_tuned_tile(tmp_path, monkeypatch):
                 assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][1], got[2][1])
                 ways.add((m, got[0][0]["tile"] == 1))
     assert len(ways) == 7, ways
+
+
+def test_a_launched_estimate_holds_no_layout(monkeypatch):
+    """Widths around the rule's line on a matrix of unequal values, a fresh
+    context each: a launched call holds what it holds without the chip."""
+    _say("case no layout held by launched estimates")
+    n, e = synth.erdos_renyi(15000, 10.0, 3)
+    g = vne.laplacian_from_edges(n, e, np.float32)
+    val = np.where(g["values"] < 0, -1.0 - (np.arange(g["values"].size) % 5), g["values"]).astype(np.float32)
+    launched = 0
+    for m in range(12, 72, 4):
+        held = []
+        for env in ("0", None):
+            monkeypatch.setenv("VNE_RESIDENT", env) if env else monkeypatch.delenv("VNE_RESIDENT")
+            with vne.Context(0) as c:
+                gid = c.register(g["row_ptr"], g["col_idx"], val, g["scale"])
+                c.estimate(gid, vne.PROBE_RADEMACHER, m, 4, 0, seed=1)
+                held.append((c.memory(), c.last_plan()["tile"]))
+        if held[1][1] >= 4:
+            launched += 1
+            assert held[0][0] == held[1][0], (m, held)
+    assert launched > 0
