@@ -13,6 +13,7 @@
 
 #include "internal.h"
 #include "kernels.h"
+#include "resident_layout.h"
 
 namespace vne {
 namespace rt {
@@ -70,8 +71,6 @@ struct DevLayout {
     int32_t waves = 0, rounds = 0, positions = 0;
     bool unit = false;
     double off_value = 0.0;
-    int64_t gathers = 0;
-    bool there = false;              // its arrays are on the device
     DevBuf slices, words, vals, spans, row_of, diag;
 };
 
@@ -91,8 +90,9 @@ struct Graph {
     double fro2 = 0.0;                       // ||A||_F^2 = tr(A^2) for symmetric A
     double trace = 0.0;
     int in_use = 0;                          // queries of a running server on this graph
-    // on-chip layouts by (waves, FP64); null: the rows do not fit.  Their arrays
-    // go to the device for the first run that takes them.
+    // by (waves, FP64): what an on-chip layout would look like (0 waves: the
+    // rows do not fit), and those that runs take
+    std::map<std::pair<int, int>, ResidentShape> shapes;
     std::map<std::pair<int, int>, std::unique_ptr<DevLayout>> layouts;
 };
 

@@ -113,6 +113,13 @@ static void front_costs(Schedule &s) {
     }
 }
 
+double step_bytes_us(int64_t n, int64_t nnz, int m_pad, int mt, bool fp64, double *gather_us) {
+    const int es = fp64 ? 8 : 4;
+    const double g = (double)(m_pad / mt) * (double)nnz * (4.0 + es + std::max(mt * es, 128)) / 6.5e6;
+    if (gather_us) *gather_us = g;
+    return 6.0 * (double)n * m_pad * es / 6.5e6 + g;
+}
+
 bool long_rows_first(const Schedule &s, int64_t nnz, int m_pad, int mt, bool fp64) {
     if (s.n_long == 0) return false;
     // Front blocks save a launch and its chain of sums (5 to 10 us a step, and
@@ -131,20 +138,18 @@ bool long_rows_first(const Schedule &s, int64_t nnz, int m_pad, int mt, bool fp6
     //    columns 54 / 45), sooner where they are little more than a segment
     //    (ER of average degree 50, 64 columns 108 / 120), or where they are
     //    many beside the step's time.
-    const int es = fp64 ? 8 : 4, lanes = mt / (fp64 ? 2 : mt % 3 == 0 ? 3 : 4), tiles = m_pad / mt;
+    const int lanes = mt / (fp64 ? 2 : mt % 3 == 0 ? 3 : 4);
     int i = 0;
     while (i + 1 < kLaneClasses && (2 << i) <= lanes) ++i;
     const bool narrow = !fp64 && lanes <= 8;
     const double share = (double)(s.long_entries + 4 * (int64_t)s.n_seg) / (double)(nnz + 4 * s.n_rows);
     const double mean = (double)s.long_entries / s.n_long;
     if (share > (mean < 96.0 ? 0.02 : narrow ? 0.25 : 0.17)) return false;
-    // the step by its bytes at 6.5 TB/s (six streams of the block; per tile
-    // the matrix and a gather of at least a line per entry) and its launches
-    const double step_us = 15.0 + (6.0 * (double)s.n_rows * m_pad * es +
-                                   (double)tiles * (double)nnz * (4.0 + es + std::max(mt * es, 128))) / 6.5e6;
+    const double step_us = 15.0 + step_bytes_us(s.n_rows, nnz, m_pad, mt, fp64);      // 15: its launches
     const double round_us = lanes <= 2 ? 15.0 : fp64 ? (lanes <= 8 ? 9.0 : 5.6) : (lanes <= 8 ? 8.0 : 6.6);
     const double chain_us = round_us * s.front[i].most + 0.05 * s.most_segs;
-    return chain_us < std::max(round_us + 3.0, 0.45 * step_us) && tiles * s.front[i].idle < 16.0 * step_us;
+    return chain_us < std::max(round_us + 3.0, 0.45 * step_us) &&
+           m_pad / mt * s.front[i].idle < 16.0 * step_us;
 }
 
 Schedule build_schedule(const int32_t *row_ptr, int64_t n, int32_t seg_len, int64_t cost_per_block,

@@ -69,6 +69,11 @@ Schedule stack_schedules(const std::vector<Schedule> &parts, const std::vector<i
                          const std::vector<int64_t> &nnz_offset, std::vector<int32_t> *graph_block_begin,
                          std::vector<int32_t> *graph_long_begin, std::vector<int32_t> *block_graph);
 
+// us of a launched step over m_pad columns in tiles of mt by its bytes at 6.5
+// TB/s: six streams of the block, and per tile the matrix and a gather of at
+// least a line per entry (gather_us: that part).
+double step_bytes_us(int64_t n, int64_t nnz, int m_pad, int mt, bool fp64, double *gather_us = nullptr);
+
 // Whether the long rows of a step over m_pad columns in tiles of mt run at the
 // front of its grid (the results are the same bits either way).
 bool long_rows_first(const Schedule &s, int64_t nnz, int m_pad, int mt, bool fp64);

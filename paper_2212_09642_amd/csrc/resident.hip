@@ -500,10 +500,13 @@ hipError_t launch(const Launch &l) {
     return hipGetLastError();
 }
 
+// (two FP64 columns take equal off-diagonal values only)
 template <typename T, int C>
 hipError_t launch_cols(const Launch &l) {
-    if (l.kind.big) return l.kind.unit ? launch<T, C, true, true>(l) : launch<T, C, false, true>(l);
-    return l.kind.unit ? launch<T, C, true, false>(l) : launch<T, C, false, false>(l);
+    if (l.kind.unit) return l.kind.big ? launch<T, C, true, true>(l) : launch<T, C, true, false>(l);
+    if constexpr (sizeof(T) == 4 || C == 1)
+        return l.kind.big ? launch<T, C, false, true>(l) : launch<T, C, false, false>(l);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_kind(const Launch &l) {

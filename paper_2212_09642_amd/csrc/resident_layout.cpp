@@ -6,37 +6,47 @@
 
 namespace vne {
 
-bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
-                           int32_t max_rounds, ResidentLayout *out, bool fp64) {
+namespace {
+
+// a row's entries in words (its own entry is not among them when unit)
+std::vector<int32_t> row_lengths(const int32_t *row_ptr, const int32_t *col, int64_t n, bool unit) {
+    std::vector<int32_t> len(n);
+    for (int64_t i = 0; i < n; ++i) {
+        int32_t c = row_ptr[i + 1] - row_ptr[i];
+        if (unit)
+            for (int32_t p = row_ptr[i]; p < row_ptr[i + 1]; ++p) c -= col[p] == i;
+        len[i] = c;
+    }
+    return len;
+}
+
+// Shape, rows by falling length and the number of long ones; false: does not fit.
+bool shape_rows(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
+                int32_t max_rounds, bool fp64, ResidentShape *s, std::vector<int32_t> *lengths,
+                std::vector<int32_t> *by_length, int64_t *long_rows) {
     if (n < 1 || waves < 1 || waves > 16 || n > (int64_t)waves * max_rounds * 64) return false;
-    ResidentLayout L;
-    L.waves = waves;
+    s->waves = waves;
     // one value for every off-diagonal entry?
-    L.unit = true;
+    s->unit = true;
     bool seen = false;
-    for (int64_t i = 0; i < n && L.unit; ++i)
+    for (int64_t i = 0; i < n && s->unit; ++i)
         for (int32_t p = row_ptr[i]; p < row_ptr[i + 1]; ++p) {
             if (col[p] == i) continue;
             if (!seen) {
-                L.off_value = val[p];
+                s->off_value = val[p];
                 seen = true;
-            } else if (val[p] != L.off_value) {
-                L.unit = false;
+            } else if (val[p] != s->off_value) {
+                s->unit = false;
                 break;
             }
         }
-    // entries of a row in words (its own entry is not among them when unit)
-    std::vector<int32_t> len(n);
+    *lengths = row_lengths(row_ptr, col, n, s->unit);
+    const std::vector<int32_t> &len = *lengths;
     int64_t total = 0;
-    for (int64_t i = 0; i < n; ++i) {
-        int32_t c = row_ptr[i + 1] - row_ptr[i];
-        if (L.unit)
-            for (int32_t p = row_ptr[i]; p < row_ptr[i + 1]; ++p) c -= col[p] == i;
-        len[i] = c;
-        total += c;
-    }
+    for (int32_t c : len) total += c;
     // rows by falling length; the ones above half a wave's share are long
-    std::vector<int32_t> order(n);
+    std::vector<int32_t> &order = *by_length;
+    order.resize(n);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return len[a] > len[b]; });
     const int64_t long_min = std::max<int64_t>(32, total / 64 / waves / 2);
@@ -44,12 +54,55 @@ bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const dou
     while (n_long < n && len[order[n_long]] > long_min) ++n_long;
     n_long = std::min<int64_t>(n_long, 64 * (int64_t)waves);
     const int64_t n_short = (n - n_long + 63) / 64;
-    L.rounds = (int32_t)((n_long > 0 ? 1 : 0) + (n_short + waves - 1) / waves);
-    if (L.rounds > max_rounds || L.positions() > kResidentMaxPositions) return false;
-    int64_t word_rows = kResidentSpareRows;
-    for (int64_t q = 0; q < n_long; ++q) word_rows += (len[order[q]] + 127) / 128;
-    for (int64_t a = n_long; a < n; a += 64) word_rows += (len[order[a]] + 3) / 4 * 2;
-    if (word_rows > resident_max_word_rows(L.unit, fp64)) return false;
+    s->rounds = (int32_t)((n_long > 0 ? 1 : 0) + (n_short + waves - 1) / waves);
+    if (s->rounds > max_rounds || s->positions() > kResidentMaxPositions) return false;
+    // (long rows are dealt to the waves in turn)
+    s->wave_long = (int32_t)((n_long + waves - 1) / waves);
+    std::vector<int64_t> tail(waves, 0);
+    s->word_rows = kResidentSpareRows;
+    for (int64_t q = 0; q < n_long; ++q) {
+        const int64_t words = (len[order[q]] + 127) / 128;
+        s->word_rows += words;
+        tail[q % waves] += words - 1;
+    }
+    s->wave_tail = *std::max_element(tail.begin(), tail.end());
+    for (int64_t a = n_long; a < n; a += 64) s->word_rows += (len[order[a]] + 3) / 4 * 2;
+    *long_rows = n_long;
+    return s->word_rows <= resident_max_word_rows(s->unit, fp64);
+}
+
+}  // namespace
+
+bool resident_shape(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
+                    int32_t max_rounds, bool fp64, ResidentShape *out) {
+    std::vector<int32_t> len, order;
+    int64_t n_long = 0;
+    ResidentShape s;
+    if (!shape_rows(row_ptr, col, val, n, waves, max_rounds, fp64, &s, &len, &order, &n_long)) return false;
+    *out = s;
+    return true;
+}
+
+double resident_step_us(const ResidentShape &s, int cols, bool fp64) {
+    // Fitted to 1224 measured steps (ER, weighted ER, preferential attachment
+    // and rings with hubs, 500 to 39 000 rows, degrees 4 to 200, 1 to 600
+    // columns; within a quarter but for a few): the step's two barriers and
+    // serial scalars, a pass over a wave's rows, the reads of v_j, and in the
+    // slowest wave a sum over the lanes per long row and a dependent load per
+    // further word of one.
+    const bool wide = cols * (fp64 ? 8 : 4) > 8;
+    const double word = s.unit ? (wide ? 12.0 : 5.7) : fp64 ? 12.0 : wide ? 20.0 : cols == 2 ? 13.0 : 9.5;
+    const double row = 0.2 * cols * (s.unit ? 1.0 : 2.0);
+    return 1.8 + 0.6 * s.rounds + word * (double)s.word_rows / 1000.0 + row * s.wave_long + 0.27 * (double)s.wave_tail;
+}
+
+bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
+                           int32_t max_rounds, ResidentLayout *out, bool fp64) {
+    ResidentLayout L;
+    std::vector<int32_t> len, order;
+    int64_t n_long = 0;
+    if (!shape_rows(row_ptr, col, val, n, waves, max_rounds, fp64, &L, &len, &order, &n_long)) return false;
+    const int64_t n_short = (n - n_long + 63) / 64;
     // slices to waves: long rows in turn, then the short slices, longest
     // first, to the wave with the least work that has room
     std::vector<std::vector<std::pair<int64_t, int64_t>>> of_wave(waves);   // {first in order, rows}, -1 - w: long
@@ -115,7 +168,6 @@ bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const dou
                 sl[0] = 1;
                 sl[1] = (int32_t)first;
                 sl[2] = words;
-                L.gathers += 2 * words;
                 for (int l = 0; l < 64; ++l) {
                     if (rows[l] < 0) continue;
                     int e = 0;
@@ -133,8 +185,7 @@ bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const dou
                     const size_t first = grow(words);
                     L.spans.push_back((int32_t)first);
                     L.spans.push_back(words);
-                    L.gathers += 2 * words;
-                    int e = 0;
+                        int e = 0;
                     for (int32_t p = row_ptr[rows[l]]; p < row_ptr[rows[l] + 1]; ++p) {
                         if (L.unit && col[p] == rows[l]) continue;
                         put((first + e / 128) * 64 + (e % 128) / 2, e & 1, (uint32_t)pos[col[p]], val[p]);

@@ -24,18 +24,23 @@ namespace vne {
 // unit: every off-diagonal entry has the value off_value; words hold the
 // off-diagonal entries only and diag the diagonal.  Otherwise words hold
 // every entry and vals its value, two per word.
-struct ResidentLayout {
+struct ResidentShape {
     int32_t waves = 0, rounds = 0;
     bool unit = false;
     double off_value = 0.0;
-    int64_t gathers = 0;                 // 64-lane reads of v_j per step
+    int64_t word_rows = 0;               // 64 words each: one 64-lane read of v_j per half
+    int32_t wave_long = 0;               // most long rows of a wave
+    int64_t wave_tail = 0;               // most words of a wave's long rows past each row's first
+    int32_t positions() const { return waves * rounds * 64; }
+};
+
+struct ResidentLayout : ResidentShape {
     std::vector<int32_t> slices;         // [waves * rounds][4]
     std::vector<uint32_t> words;
     std::vector<double> vals;            // [2 * words] or empty
     std::vector<int32_t> spans;
     std::vector<int32_t> row_of;         // [positions] row, or -1
     std::vector<double> diag;            // [positions] (unit) or empty
-    int32_t positions() const { return waves * rounds * 64; }
 };
 
 // Word rows of padding behind the last slice: the kernel loads the words of
@@ -51,6 +56,13 @@ constexpr int32_t kResidentMaxPositions = 65472;
 constexpr int64_t resident_max_word_rows(bool unit, bool fp64) {
     return (int64_t(1) << 32) / (unit ? 256 : fp64 ? 64 * 16 : 64 * 8);
 }
+
+// What the layout of build_resident_layout looks like, without it.
+bool resident_shape(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
+                    int32_t max_rounds, bool fp64, ResidentShape *out);
+
+// us of one on-chip step of a workgroup with `cols` columns.
+double resident_step_us(const ResidentShape &s, int cols, bool fp64);
 
 // Layout for `waves` wavefronts (1 .. 16) and vectors of the given type.
 // Returns false when the rows need more than max_rounds rounds, or more word

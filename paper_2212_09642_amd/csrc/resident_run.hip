@@ -38,59 +38,77 @@ bool put(vne_ctx *c, DevBuf *b, const std::vector<T> &h) {
     return h.empty() || hipMemcpy(b->p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
 }
 
-bool build(const Graph *g, int waves, bool fp64, ResidentLayout *h) {
-    return build_resident_layout(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves,
-                                 fp64 ? kResidentSlots64 : kResidentSlots32, h, fp64);
+int slots(bool fp64) { return fp64 ? kResidentSlots64 : kResidentSlots32; }
+
+// The shape of graph gid's layout for a workgroup of `waves`; null: does not fit.
+const ResidentShape *shape_of(vne_ctx *c, int32_t gid, int waves, bool fp64) {
+    Graph *g = get_graph(c, gid);
+    const auto key = std::make_pair(waves, (int)fp64);
+    auto it = g->shapes.find(key);
+    if (it == g->shapes.end()) {
+        ResidentShape s;
+        if (!resident_shape(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves, slots(fp64), fp64, &s) ||
+            resident_lds(s.positions(), 1, fp64) > kResidentLds)
+            s = ResidentShape();
+        it = g->shapes.emplace(key, s).first;
+    }
+    return it->second.waves > 0 ? &it->second : nullptr;
 }
 
-// The layout of graph gid for a workgroup of `waves`, without its arrays; null:
-// does not fit.
+// The layout itself, for a run that takes it; null: does not fit, or no room.
 DevLayout *layout_of(vne_ctx *c, int32_t gid, int waves, bool fp64) {
+    if (!shape_of(c, gid, waves, fp64)) return nullptr;
     Graph *g = get_graph(c, gid);
     const auto key = std::make_pair(waves, (int)fp64);
     auto it = g->layouts.find(key);
     if (it != g->layouts.end()) return it->second.get();
-    auto &slot = g->layouts[key];
     ResidentLayout h;
-    if (!build(g, waves, fp64, &h)) return nullptr;
-    if (resident_lds(h.positions(), 1, fp64) > kResidentLds) return nullptr;
+    if (!build_resident_layout(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves, slots(fp64), &h,
+                               fp64))
+        return nullptr;
     auto d = std::make_unique<DevLayout>();
     d->waves = waves;
     d->rounds = h.rounds;
     d->positions = h.positions();
     d->unit = h.unit;
     d->off_value = h.off_value;
-    d->gathers = h.gathers;
-    slot = std::move(d);
-    return slot.get();
-}
-
-// Its arrays to the device; false: no room (the launched steps run, and a later
-// call may try again).
-bool bring(vne_ctx *c, int32_t gid, DevLayout *d, bool fp64) {
-    if (d->there) return true;
-    ResidentLayout h;
-    if (!build(get_graph(c, gid), d->waves, fp64, &h)) return false;
     const std::string err = c->err;
     bool ok = put(c, &d->slices, h.slices) && put(c, &d->words, h.words) && put(c, &d->spans, h.spans) &&
               put(c, &d->row_of, h.row_of) && put(c, &d->diag, h.diag);
     if (ok && !h.unit)
         ok = fp64 ? put(c, &d->vals, h.vals) : put(c, &d->vals, std::vector<float>(h.vals.begin(), h.vals.end()));
     if (!ok) {
+        // no room: the launched steps run, and a later call may try again
         for (DevBuf *b : {&d->slices, &d->words, &d->vals, &d->spans, &d->row_of, &d->diag}) dev_free(c, b);
         c->err = err;
+        return nullptr;
     }
-    return d->there = ok;
+    return (g->layouts[key] = std::move(d)).get();
 }
 
-// the widest column group (at most cap) that the layout has room for
-int widest(const DevLayout *L, bool fp64, int cap) {
-    int cols = cap;
-    while (cols > 1 && (L->rounds * cols > (fp64 ? kResidentSlots64 : kResidentSlots32) ||
-                        resident_lds(L->positions, cols, fp64) > kResidentLds))
+// the widest column group (at most cap) that the layout has room for (two FP64
+// columns of unequal values spill: 5000 rows of 10, 600 columns, us a step: 55
+// against 3 x 10)
+int widest(const ResidentShape &s, bool fp64, int cap) {
+    int cols = fp64 && !s.unit ? 1 : cap;
+    while (cols > 1 && (s.rounds * cols > slots(fp64) || resident_lds(s.positions(), cols, fp64) > kResidentLds))
         cols /= 2;
     return cols;
 }
+
+// us of a launched step of one matrix or of a stack of them, by sizes alone,
+// fitted to the launched times of the pairs that resident_step_us was fitted to
+// (mean deviation 12%): its launches and dependent reductions (base), the
+// streams, the gathers (of blocks that caches hold), more of both for long
+// rows, and the rows' share of the reductions.
+double launched_us(double base, int64_t n, int64_t nnz, int64_t long_entries, int m, bool fp64) {
+    const int mt = choose_plan_tile(m, fp64, n, nnz);
+    double gather = 0.0;
+    const double streams = step_bytes_us(n, nnz, pad_columns(m, mt), mt, fp64, &gather) - gather;
+    const double share = (double)long_entries / (double)std::max<int64_t>(1, nnz);
+    return base + 1.1 * streams + (0.45 + 0.65 * share) * gather + (long_entries > 0 ? 3.5 : 0.0) + 0.8e-4 * (double)n;
+}
+constexpr double kLaunchUs = 16.0, kStackLaunchUs = 20.0;
 
 ResidentJob job_of(const GraphSet *one, const DevLayout *L, const Graph *g, bool fp64) {
     ResidentJob j{};
@@ -148,43 +166,45 @@ DevLayout *chip_choice(vne_ctx *c, GraphSet *set, const Plan *p, int *cols) {
     // (with a memory budget the launched steps, whose allocations do not
     // depend on the matrix's size or the rule)
     if (mode == 0 || c->budget != 0 || set->G != 1 || set->n > lds_elements(p->fp64)) return nullptr;
+    const bool fp64 = p->fp64;
     const int waves = (int)std::min<int64_t>(16, (set->n + 63) / 64);
     // one column per workgroup while a CU each is left, then as many as fit
-    const int es = p->fp64 ? 8 : 4;
     int cap = 1;
-    while (cap < (p->fp64 ? 2 : 4) && (p->m + cap - 1) / cap > 256) cap *= 2;
-    // A step on the chip: its 64-lane gathers on one CU at about 20 cycles
-    // (30 for four columns at once) and 1.5 us of serial work, per round of
-    // 256 workgroups.  A launched step: about 15 us of launches and
-    // dependent reductions, and its bytes at 6.5 TB/s.  So few columns of a
-    // large matrix, which leave most CUs idle on the chip, are launched.
-    // Measured (us a step, launched / chip): ER n = 2000, 30 columns FP64
-    // 14.7 / 3.5; BA n = 12000, 300 columns 74 / 26; WS n = 12000, 21 columns
-    // FP64 19.8 / 15.1; BA n = 36000, 64 columns 44 / 47; ER n = 39000, 8
-    // columns 22 / 46.
-    // (the sizes alone decide, never a tile that was tuned: every call of a
-    // shape runs the same way)
-    const int mt = choose_plan_tile(p->m, p->fp64, set->n, set->nnz), m_pad = pad_columns(p->m, mt);
-    auto slower = [&](double gathers, int columns) {
+    while (cap < (fp64 ? 2 : 4) && (p->m + cap - 1) / cap > 256) cap *= 2;
+    // A step on the chip, per round of 256 workgroups, against a launched
+    // one; the sizes alone decide, never a tile that was tuned, so that every
+    // call of a shape runs the same way.  Few columns of a large matrix, which
+    // leave most CUs idle on the chip, are launched.  Measured (us a step,
+    // launched / chip): ER n = 2000, 30 columns FP64 14.7 / 3.5; BA n = 12000,
+    // 300 columns 74 / 26; WS n = 12000, 21 columns FP64 19.8 / 15.1; ER n =
+    // 39000, 8 columns 18 / 40, 64 columns 32 / 40, 256 columns 81 / 39; a ring
+    // of 30000 rows with one of 15000 entries, 8 columns 29 / 83.  Over 1224
+    // such pairs the rule is 0.8% from the faster way; in five of them the
+    // chip is taken where it is 11 to 22% slower.
+    const double launched =
+        launched_us(kLaunchUs, set->n, set->nnz, set->sched.long_entries, p->m, fp64);
+    auto slower = [&](const ResidentShape &s, int columns) {
         const double rounds = std::ceil(std::ceil((double)p->m / columns) / 256.0);
-        const double chip = rounds * (1.5 + gathers * (columns * es > 8 ? 30.0 : 20.0) / 2400.0);
-        const double bytes = 6.0 * (double)set->n * m_pad * es +
-                             (double)(m_pad / mt) * (double)set->nnz * (4.0 + es + std::max(mt * es, 128));
-        return mode != 1 && chip > 15.0 + bytes / 6.5e6;
+        return mode != 1 && rounds * resident_step_us(s, columns, fp64) > launched;
     };
-    // (no layout is built where even full slices would be slower)
-    if (slower((double)(set->nnz - set->n) / 64.0, cap)) return nullptr;
-    DevLayout *L = layout_of(c, set->ids[0], waves, p->fp64);
-    if (!L) return nullptr;
-    *cols = widest(L, p->fp64, cap);
-    return !slower((double)L->gathers, *cols) && bring(c, set->ids[0], L, p->fp64) ? L : nullptr;
+    // (the shape is not looked for where even full slices would be slower)
+    ResidentShape full;
+    full.unit = true;
+    full.rounds = (int32_t)((set->n + 64 * waves - 1) / (64 * waves));
+    full.word_rows = (set->nnz - set->n) / 128;
+    if (slower(full, cap)) return nullptr;
+    const ResidentShape *s = shape_of(c, set->ids[0], waves, fp64);
+    if (!s) return nullptr;
+    *cols = widest(*s, fp64, cap);
+    return slower(*s, *cols) ? nullptr : layout_of(c, set->ids[0], waves, fp64);
 }
 
 DevLayout *chip_layout(vne_ctx *c, int32_t gid, int max_rounds) {
     const Graph *g = get_graph(c, gid);
     if (chip_mode() == 0 || c->budget != 0 || g->n > (int64_t)1024 * max_rounds) return nullptr;
-    DevLayout *L = layout_of(c, gid, (int)std::min<int64_t>(16, (g->n + 63) / 64), true);
-    return L && L->rounds <= max_rounds && bring(c, gid, L, true) ? L : nullptr;
+    const int waves = (int)std::min<int64_t>(16, (g->n + 63) / 64);
+    const ResidentShape *s = shape_of(c, gid, waves, true);
+    return s && s->rounds <= max_rounds ? layout_of(c, gid, waves, true) : nullptr;
 }
 
 vne_status run_chip(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, bool desing, const DevLayout *L,
@@ -235,6 +255,7 @@ struct ChipBatch {
     int combine = 0;
     std::vector<DevLayout *> layout;
     std::vector<int> cols;
+    std::vector<double> step_us;
     struct Class {
         int waves;
         ResidentKind kind;
@@ -369,7 +390,7 @@ vne_status chip_args(vne_ctx *c, ChipBatch *b, bool desing) {
         const int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(32, total / 64));
         for (int q : members[k]) {
             const int groups = (jobs[q].m + cl.kind.cols - 1) / cl.kind.cols;
-            const double each = ((double)b->layout[q]->gathers + 400.0) * jobs[q].k;
+            const double each = b->step_us[q] * jobs[q].k;
             for (int f = 0; f < groups; f += chunk)
                 runs.push_back({each * std::min(chunk, groups - f), q, f, std::min(chunk, groups - f)});
         }
@@ -414,7 +435,7 @@ vne_status chip_args(vne_ctx *c, ChipBatch *b, bool desing) {
 vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_probes *pr, const int32_t *k_steps,
                          bool fp64, bool desing, vne_result *out) {
     const int n_queries = (int)ids.size();
-    // the graphs that go on the chip, their layouts and column groups.  With
+    // The graphs that go on the chip, their layouts and column groups.  With
     // a memory budget every graph is stacked, so that what a budget admits
     // does not depend on the matrices' sizes.
     std::vector<int> small, large;
@@ -444,28 +465,82 @@ vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_
         // every CU wants two workgroups to go to
         int cap = fp64 ? 2 : 4;
         while (cap > 1 && columns / cap < 512) cap /= 2;
+        // the smallest workgroup whose registers hold a graph's share: several
+        // then share a CU and hide each other's barriers
+        struct Fit {
+            int q, waves, cols, groups;
+            double us;                   // of a step of one workgroup
+            double share;                // of a CU's time that the workgroup takes
+        };
+        std::vector<Fit> fits;
         for (int q = 0; q < n_queries; ++q) {
             const int64_t gn = get_graph(c, ids[q])->n;
-            DevLayout *L = nullptr;
-            int cols = cap;
-            // the smallest workgroup whose registers hold its share: several
-            // then share a CU and hide each other's barriers
-            for (; gn <= room && !L && cols >= 1; cols /= 2) {
-                for (int waves = 4; waves <= 16 && !L; waves *= 2) {
+            bool found = false;
+            for (int cols = cap; gn <= room && !found && cols >= 1; cols /= 2)
+                for (int waves = 4; waves <= 16 && !found; waves *= 2) {
                     if (gn * cols * 16 > room * waves) continue;
                     const int w = (int)std::min<int64_t>(waves, (gn + 63) / 64);
-                    L = layout_of(c, ids[q], w, fp64);
-                    if (L && widest(L, fp64, cols) < cols) L = nullptr;
+                    const ResidentShape *s = shape_of(c, ids[q], w, fp64);
+                    if (!s || widest(*s, fp64, cols) < cols) continue;
+                    // (two or more on a CU overlap: 0.55 of the lone time each)
+                    const bool alone = 2 * resident_lds(s->positions(), cols, fp64) > kResidentLds;
+                    fits.push_back({q, w, cols, (pr[q].m + cols - 1) / cols, resident_step_us(*s, cols, fp64),
+                                    alone ? 1.0 : 0.55});
+                    found = true;
                 }
-                if (L) break;
+            if (!found) large.push_back(q);
+        }
+        // Which of them run on the chip: the ones whose workgroups are slowest
+        // go to the stack first, as many as make the call shortest.  The chip
+        // runs behind the stacked steps, so that a stack that is there anyway
+        // takes small graphs of few columns almost for nothing (8 graphs of 1000 to
+        // 50 000 rows, FP64, 4 columns: us a step all that fit on the chip 58,
+        // all stacked 44), and a batch without one is fastest on the chip
+        // (128 graphs of 1000 rows, 16 columns: 42 stacked, 8.8).
+        std::stable_sort(fits.begin(), fits.end(),
+                         [&](const Fit &x, const Fit &y) { return x.us * k_steps[x.q] > y.us * k_steps[y.q]; });
+        size_t first = 0;                // fits[first ..] on the chip
+        if (chip_mode() != 1) {
+            int64_t sn = 0, snnz = 0, slong = 0;
+            int sm = 0, sk = 0, sg = 0;
+            auto stack = [&](int q) {
+                const Graph *g = get_graph(c, ids[q]);
+                sn += g->n;
+                snnz += g->nnz;
+                slong += g->sched.long_entries;
+                sm = std::max(sm, (int)pr[q].m);
+                sk = std::max(sk, (int)k_steps[q]);
+                ++sg;
+            };
+            for (int q : large) stack(q);
+            double work = 0.0;
+            for (const Fit &f : fits) work += f.us * f.share * f.groups * k_steps[f.q];
+            double best = 0.0;
+            for (size_t i = 0; i <= fits.size(); ++i) {
+                double us = sg == 0 ? 0.0 : sk * launched_us(sg == 1 ? kLaunchUs : kStackLaunchUs, sn, snnz, slong, sm, fp64);
+                if (i < fits.size()) us += std::max(fits[i].us * k_steps[fits[i].q], work / 256.0);
+                if (i == 0 || us < best) {
+                    best = us;
+                    first = i;
+                }
+                if (i == fits.size()) break;
+                work -= fits[i].us * fits[i].share * fits[i].groups * k_steps[fits[i].q];
+                stack(fits[i].q);
             }
-            if (L && bring(c, ids[q], L, fp64)) {
-                small.push_back(q);
-                b.layout.push_back(L);
-                b.cols.push_back(cols);
-            } else {
+        }
+        std::vector<const Fit *> of(n_queries, nullptr);
+        for (size_t i = first; i < fits.size(); ++i) of[fits[i].q] = &fits[i];
+        large.clear();
+        for (int q = 0; q < n_queries; ++q) {
+            DevLayout *L = of[q] ? layout_of(c, ids[q], of[q]->waves, fp64) : nullptr;
+            if (!L) {
                 large.push_back(q);
+                continue;
             }
+            small.push_back(q);
+            b.layout.push_back(L);
+            b.cols.push_back(of[q]->cols);
+            b.step_us.push_back(of[q]->us);
         }
     }
     if (small.empty()) {
