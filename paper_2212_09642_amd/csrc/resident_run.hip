@@ -620,8 +620,10 @@ vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_
                                         (const int2 *)((const char *)p->res_args.p + cl.map_at), (int)cl.map.size(),
                                         cl.waves, cl.kind, cl.lds, s));
         HIP_TRY(c, hipEventRecord(c->side_events[1 + k], s));
+        // (at once: a class whose launch fails leaves none of the others
+        // running past the call's stream)
+        HIP_TRY(c, hipStreamWaitEvent(c->stream, c->side_events[1 + k], 0));
     }
-    for (size_t k = 0; k < b.classes.size(); ++k) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->side_events[1 + k], 0));
     if (c->timing) {
         HIP_TRY(c, hipEventRecord(p->ev[1], c->stream));
         c->pending.push_back({p, step_bytes(b.set, p) + (lp ? step_bytes(ls, lp) : 0.0), std::max(p->k, lp ? lp->k : 0),
