@@ -313,7 +313,9 @@ typedef struct {
     double eps_hat;             /* absolute target for d and for the Krylov part           */
     int64_t vector_steps;       /* sum over passes and colours of the steps used           */
     int64_t block_steps;        /* sum over passes of the steps the block ran              */
-    double color_ms, lanczos_ms;/* host colouring time; Lanczos passes (wall, synchronised) */
+    double color_ms, lanczos_ms;/* host colouring time; Lanczos passes (wall, synchronised).
+                                   The heuristic's three colourings run beside its
+                                   passes, so that the two may add up to more than the call */
     int32_t *colors;            /* host [n] or NULL: colouring of the final pass           */
     double *quad;               /* host [quad_cap] or NULL: psi of the final pass          */
     int32_t *steps;             /* host [quad_cap] or NULL: stop step per colour (0: k_max
@@ -441,7 +443,10 @@ vne_status vne_error_bounds(vne_ctx *ctx, int32_t m, int32_t k, const double *al
  * reset != 0 clears) the number of timed launches, their total milliseconds
  * and the algorithmic bytes those launches were due to move (CSR once, the
  * gathered block once, the previous block once, the new block once per
- * step).  Timing adds one event pair per launch and no synchronization
+ * step).  Runs inside workgroups count their steps as launches and the bytes
+ * that launched steps would be due to move, although their blocks stay on the
+ * chip; a batch with such runs is timed as one span of as many launches as its
+ * longest part has steps, with the bytes of each part's own steps.  Timing adds one event pair per launch and no synchronization
  * inside a call. */
 vne_status vne_enable_kernel_timing(vne_ctx *ctx, int32_t enable);
 vne_status vne_kernel_timing(vne_ctx *ctx, int32_t reset, int64_t *launches, double *total_ms,

@@ -626,8 +626,10 @@ vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_
     }
     if (c->timing) {
         HIP_TRY(c, hipEventRecord(p->ev[1], c->stream));
-        c->pending.push_back({p, step_bytes(b.set, p) + (lp ? step_bytes(ls, lp) : 0.0), std::max(p->k, lp ? lp->k : 0),
-                              true});
+        // one span: the bytes of either part's own steps, over the longer one's
+        const int steps = std::max(p->k, lp ? lp->k : 0);
+        const double bytes = step_bytes(b.set, p) * p->k + (lp ? step_bytes(ls, lp) * lp->k : 0.0);
+        c->pending.push_back({p, bytes / steps, steps, true});
     }
     HIP_TRY(c, launch_quadrature((const double *)p->alpha.p, (const double *)p->beta.p, (const int32_t *)p->k_eff.p,
                                  (const double *)p->norm2.p, p->k, p->k, p->G * p->m_pad, (double *)p->psi.p,

@@ -75,3 +75,26 @@ def test_batches_of_few_and_many_columns(ctx, fp64, m):
             assert np.array_equal(a[key], b[key]), key
     for gid, _ in regs:
         ctx.release(gid)
+
+
+def test_timed_bytes_are_each_parts_own(ctx):
+    """A batch on the chip and stacked, of different step counts: each part's
+    bytes a step over its own steps."""
+    _say("case timed bytes of a mixed batch")
+    regs = [_setup(ctx, *synth.watts_strogatz(n, 6, 0.1, n), False) for n in (1500, 3000, 41000)]
+    q = [dict(gid=gid, kind=vne.PROBE_RADEMACHER, m=64, k=k, seed=1) for (gid, _), k in zip(regs, (30, 30, 5))]
+    ctx.estimate_batch(q, _mode(False))
+    ctx.enable_kernel_timing(True)
+    ctx.kernel_timing(reset=True)
+    ctx.estimate_batch(q, _mode(False))
+    got = ctx.kernel_timing(reset=True)
+    ctx.enable_kernel_timing(False)
+
+    def step(parts):
+        n, nnz = sum(ref.n for _, ref in parts), sum(ref.col_idx.size for _, ref in parts)
+        return 4.0 * (n + 1) + 8.0 * nnz + 3.0 * 4.0 * 64 * n
+
+    want = 30 * step(regs[:2]) + 5 * step(regs[2:])
+    assert got["launches"] == 30 and abs(got["bytes"] - want) <= 1e-9 * want, (got, want)
+    for gid, _ in regs:
+        ctx.release(gid)
