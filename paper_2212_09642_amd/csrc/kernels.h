@@ -196,17 +196,17 @@ hipError_t launch_rademacher_fill(void *out, bool fp64, int32_t n, int32_t m, in
                                   hipStream_t s);
 
 // Gauss quadrature of every column after min(k_eff[c], steps) steps:
-// psi[c] = norm2[c] e1^T f(T) e1 (1 <= steps <= k).  With `stop` given, a
-// record {uid, j > 0} there lowers steps to j (a-posteriori stopping); with
-// col_stop given, col_stop[c] > 0 lowers column c's steps to it.  fp64: the
-// coefficients come from FP64 vectors (tighter limit on the shift of the
-// integral route, see kernels.hip).
+// psi[c] = norm2[c] e1^T f(T) e1 (1 <= steps <= k).  With col_stop given,
+// col_stop[c] > 0 lowers column c's steps to it (a-posteriori stopping).
+// fp64: the coefficients come from FP64 vectors (tighter limit on the shift of
+// the integral route, see kernels.hip).
 hipError_t launch_quadrature(const double *alpha, const double *beta, const int32_t *k_eff,
                              const double *norm2, int32_t k, int32_t steps, int32_t m, double *psi,
-                             int32_t *flags, hipStream_t s, bool fp64, const int2 *stop = nullptr,
-                             int32_t uid = 0, const int32_t *col_stop = nullptr, int32_t *steps_out = nullptr);
-// The quadratures of several problems in one launch, arguments by value (jobs
-// of as launch_quadrature's; first[j]: blocks before job j's).
+                             int32_t *flags, hipStream_t s, bool fp64, const int32_t *col_stop = nullptr);
+// The quadratures of several problems in one launch, arguments by value
+// (first[j]: blocks before job j's).  A record {uid, j > 0} at `stop` lowers a
+// job's steps to j; the steps taken go to *steps_out, as the largest of the jobs
+// that share it.
 constexpr int kQuadJobs = 32;
 struct QuadJob {
     const double *alpha, *beta;
@@ -293,10 +293,9 @@ hipError_t launch_column_stop(const ColStopArgs *args, hipStream_t s);
 constexpr int kBoundGrid = 256;            // grid points of the serving loop's checks
 constexpr double kLamLoFraction = 1e-12;   // serving: lower end of the bound interval / lambda_ub
 
-// estimate from psi: kind 0 mean, 1 sum, 2 Hutch++ (first n_sketch summed,
-// rest averaged); one estimate per graph from psi[g * ld + c], c < graph_m[g]
-hipError_t launch_combine(const double *psi, int32_t m, int32_t kind, int32_t n_sketch,
-                          double *estimate, hipStream_t s);
+// estimates from psi: Hutch++ (first n_sketch summed, rest averaged); one per
+// graph from psi[g * ld + c], c < graph_m[g] (kind 0 mean, 1 sum)
+hipError_t launch_combine_hutchpp(const double *psi, int32_t m, int32_t n_sketch, double *estimate, hipStream_t s);
 hipError_t launch_combine_graphs(const double *psi, int32_t ld, const int32_t *graph_m, int32_t n_graphs,
                                  int32_t kind, double *estimates, hipStream_t s);
 

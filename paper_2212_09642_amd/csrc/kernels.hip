@@ -1819,11 +1819,10 @@ __device__ __forceinline__ void quadrature_column(const double *alpha, const dou
 __global__ void __launch_bounds__(256) k_quadrature(const double *alpha, const double *beta,
                                                     const int32_t *k_eff, const double *norm2, int32_t k,
                                                     int32_t steps, int32_t m, double *psi, int32_t *flags,
-                                                    const int2 *stop, int32_t uid, const int32_t *col_stop,
-                                                    int32_t shift_max, int32_t *steps_out) {
+                                                    const int32_t *col_stop, int32_t shift_max) {
     const int c = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
     if (c >= m) return;
-    quadrature_column(alpha, beta, k_eff, norm2, k, steps, c, psi, flags, stop, uid, col_stop, shift_max, steps_out);
+    quadrature_column(alpha, beta, k_eff, norm2, k, steps, c, psi, flags, nullptr, 0, col_stop, shift_max, nullptr);
 }
 
 // The members that end in one tick of a server together (10 us each, in turn,
@@ -2140,13 +2139,12 @@ hipError_t launch_column_stop(const ColStopArgs *args, hipStream_t s) {
 
 hipError_t launch_quadrature(const double *alpha, const double *beta, const int32_t *k_eff,
                              const double *norm2, int32_t k, int32_t steps, int32_t m, double *psi,
-                             int32_t *flags, hipStream_t s, bool fp64, const int2 *stop, int32_t uid,
-                             const int32_t *col_stop, int32_t *steps_out) {
+                             int32_t *flags, hipStream_t s, bool fp64, const int32_t *col_stop) {
     if (k > kMaxSteps || steps < 1 || steps > k) return hipErrorInvalidValue;
     // FP64 vectors: shifts up to 5e-14 (below 1e-13 relative); FP32: up to 5e-8
     const int32_t shift_max = fp64 ? 1 : 4;
     hipLaunchKernelGGL(k_quadrature, dim3((m + 3) / 4), dim3(256), 0, s, alpha, beta, k_eff, norm2, k, steps, m,
-                       psi, flags, stop, uid, col_stop, shift_max, steps_out);
+                       psi, flags, col_stop, shift_max);
     return hipGetLastError();
 }
 
@@ -2354,24 +2352,21 @@ hipError_t launch_fT_e1(const double *alpha, const double *beta, const int32_t *
 }
 
 // ---------------------------------------------------------------------------
-// estimator combine (one block, fixed order)
+// estimator combine (a block per estimate, fixed order)
 // ---------------------------------------------------------------------------
 
-__global__ void __launch_bounds__(256) k_combine(const double *psi, int32_t m, int32_t kind,
-                                                 int32_t n_sketch, double *estimate) {
+// Hutch++: the sketch's forms summed, the rest averaged
+__global__ void __launch_bounds__(256) k_combine_hutchpp(const double *psi, int32_t m, int32_t n_sketch,
+                                                         double *estimate) {
     __shared__ double sh[256];
     double a = 0.0, b = 0.0;
     for (int c = threadIdx.x; c < m; c += 256) {
-        if (kind == 2 && c < n_sketch) a += psi[c];
+        if (c < n_sketch) a += psi[c];
         else b += psi[c];
     }
     a = block_sum_256(a, sh);
     b = block_sum_256(b, sh);
-    if (threadIdx.x == 0) {
-        if (kind == 0) *estimate = b / (double)m;
-        else if (kind == 1) *estimate = b;
-        else *estimate = a + (m > n_sketch ? b / (double)(m - n_sketch) : 0.0);
-    }
+    if (threadIdx.x == 0) *estimate = a + (m > n_sketch ? b / (double)(m - n_sketch) : 0.0);
 }
 
 __device__ __forceinline__ void combine_graph(const double *psi, int32_t ld, const int32_t *graph_m, int32_t kind,
@@ -2404,7 +2399,7 @@ __global__ void __launch_bounds__(256) k_collect(CollectArgs a) {
         for (int t = first; t < a.words[q]; t += stride) a.dst[q][t] = a.src[q][t];
 }
 
-// a block per query: its forms (and their mean, as k_combine has it) and flags
+// a block per query: its forms (and their mean) and flags
 __global__ void __launch_bounds__(256) k_forms_jobs(FormsJobs a) {
     __shared__ double sh[256];
     const FormsJob &q = a.job[blockIdx.x];
@@ -2444,9 +2439,8 @@ hipError_t launch_combine_graphs(const double *psi, int32_t ld, const int32_t *g
     return hipGetLastError();
 }
 
-hipError_t launch_combine(const double *psi, int32_t m, int32_t kind, int32_t n_sketch, double *estimate,
-                          hipStream_t s) {
-    hipLaunchKernelGGL(k_combine, dim3(1), dim3(256), 0, s, psi, m, kind, n_sketch, estimate);
+hipError_t launch_combine_hutchpp(const double *psi, int32_t m, int32_t n_sketch, double *estimate, hipStream_t s) {
+    hipLaunchKernelGGL(k_combine_hutchpp, dim3(1), dim3(256), 0, s, psi, m, n_sketch, estimate);
     return hipGetLastError();
 }
 

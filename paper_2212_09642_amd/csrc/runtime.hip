@@ -706,7 +706,7 @@ vne_status run_lanczos(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, 
         if (timing) c->pending.push_back({p, bytes, ran});
         HIP_TRY(c, launch_quadrature((const double *)p->alpha.p, (const double *)p->beta.p,
                                      (const int32_t *)p->k_eff.p, (const double *)p->norm2.p, K, K, p->m_pad,
-                                     (double *)p->psi.p, (int32_t *)p->flags.p, c->stream, p->fp64, nullptr, 0,
+                                     (double *)p->psi.p, (int32_t *)p->flags.p, c->stream, p->fp64,
                                      (const int32_t *)p->col_stop.p));
         return VNE_OK;
     }
@@ -1066,7 +1066,7 @@ vne_status hutchpp_run(vne_ctx *c, GraphSet *set, int nr, int nh, int g_col0, in
     pq.dense = q->B.p;
     pq.ld_dense = m;
     VNE_TRY(run_lanczos(c, set, q, pq, desing));
-    HIP_TRY(c, launch_combine((const double *)q->psi.p, m, 2, nr, (double *)q->estimate.p, s));
+    HIP_TRY(c, launch_combine_hutchpp((const double *)q->psi.p, m, nr, (double *)q->estimate.p, s));
     if (sk_out) *sk_out = sk;
     *q_out = q;
     return VNE_OK;
