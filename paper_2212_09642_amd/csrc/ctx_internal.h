@@ -91,8 +91,10 @@ struct Graph {
     double trace = 0.0;
     int in_use = 0;                          // queries of a running server on this graph
     // by (waves, FP64): what an on-chip layout would look like (0 waves: the
-    // rows do not fit), and those that runs take
+    // rows do not fit), and those that runs take; shape_rows: of shapes whose
+    // first call has not decided yet
     std::map<std::pair<int, int>, ResidentShape> shapes;
+    std::map<std::pair<int, int>, ResidentRows> shape_rows;
     std::map<std::pair<int, int>, std::unique_ptr<DevLayout>> layouts;
 };
 

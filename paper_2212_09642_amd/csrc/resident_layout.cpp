@@ -2,7 +2,6 @@
 #include "resident_layout.h"
 
 #include <algorithm>
-#include <numeric>
 
 namespace vne {
 
@@ -20,11 +19,12 @@ std::vector<int32_t> row_lengths(const int32_t *row_ptr, const int32_t *col, int
     return len;
 }
 
-// Shape, rows by falling length and the number of long ones; false: does not fit.
-bool shape_rows(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
-                int32_t max_rounds, bool fp64, ResidentShape *s, std::vector<int32_t> *lengths,
-                std::vector<int32_t> *by_length, int64_t *long_rows) {
+}  // namespace
+
+bool resident_shape(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
+                    int32_t max_rounds, bool fp64, ResidentShape *s, ResidentRows *rows) {
     if (n < 1 || waves < 1 || waves > 16 || n > (int64_t)waves * max_rounds * 64) return false;
+    *s = ResidentShape();
     s->waves = waves;
     // one value for every off-diagonal entry?
     s->unit = true;
@@ -40,15 +40,22 @@ bool shape_rows(const int32_t *row_ptr, const int32_t *col, const double *val, i
                 break;
             }
         }
-    *lengths = row_lengths(row_ptr, col, n, s->unit);
-    const std::vector<int32_t> &len = *lengths;
+    rows->len = row_lengths(row_ptr, col, n, s->unit);
+    const std::vector<int32_t> &len = rows->len;
     int64_t total = 0;
-    for (int32_t c : len) total += c;
-    // rows by falling length; the ones above half a wave's share are long
-    std::vector<int32_t> &order = *by_length;
+    int32_t longest = 0;
+    for (int32_t c : len) {
+        total += c;
+        longest = std::max(longest, c);
+    }
+    // rows by falling length (counted, not compared: the first call on a graph
+    // waits for this); the ones above half a wave's share are long
+    std::vector<int32_t> &order = rows->order;
     order.resize(n);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return len[a] > len[b]; });
+    std::vector<int32_t> place((size_t)longest + 2, 0);
+    for (int32_t c : len) ++place[longest - c + 1];
+    for (int32_t q = 0; q <= longest; ++q) place[q + 1] += place[q];
+    for (int64_t i = 0; i < n; ++i) order[place[longest - len[i]]++] = (int32_t)i;
     const int64_t long_min = std::max<int64_t>(32, total / 64 / waves / 2);
     int64_t n_long = 0;
     while (n_long < n && len[order[n_long]] > long_min) ++n_long;
@@ -67,20 +74,8 @@ bool shape_rows(const int32_t *row_ptr, const int32_t *col, const double *val, i
     }
     s->wave_tail = *std::max_element(tail.begin(), tail.end());
     for (int64_t a = n_long; a < n; a += 64) s->word_rows += (len[order[a]] + 3) / 4 * 2;
-    *long_rows = n_long;
+    rows->n_long = n_long;
     return s->word_rows <= resident_max_word_rows(s->unit, fp64);
-}
-
-}  // namespace
-
-bool resident_shape(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
-                    int32_t max_rounds, bool fp64, ResidentShape *out) {
-    std::vector<int32_t> len, order;
-    int64_t n_long = 0;
-    ResidentShape s;
-    if (!shape_rows(row_ptr, col, val, n, waves, max_rounds, fp64, &s, &len, &order, &n_long)) return false;
-    *out = s;
-    return true;
 }
 
 double resident_step_us(const ResidentShape &s, int cols, bool fp64) {
@@ -98,11 +93,20 @@ double resident_step_us(const ResidentShape &s, int cols, bool fp64) {
 
 bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
                            int32_t max_rounds, ResidentLayout *out, bool fp64) {
+    ResidentShape shape;
+    ResidentRows rows;
+    if (!resident_shape(row_ptr, col, val, n, waves, max_rounds, fp64, &shape, &rows)) return false;
+    lay_out(row_ptr, col, val, n, shape, rows, out);
+    return true;
+}
+
+void lay_out(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, const ResidentShape &shape,
+             const ResidentRows &rows_of, ResidentLayout *out) {
     ResidentLayout L;
-    std::vector<int32_t> len, order;
-    int64_t n_long = 0;
-    if (!shape_rows(row_ptr, col, val, n, waves, max_rounds, fp64, &L, &len, &order, &n_long)) return false;
-    const int64_t n_short = (n - n_long + 63) / 64;
+    static_cast<ResidentShape &>(L) = shape;
+    const std::vector<int32_t> &len = rows_of.len, &order = rows_of.order;
+    const int64_t n_long = rows_of.n_long, n_short = (n - n_long + 63) / 64;
+    const int32_t waves = L.waves;
     // slices to waves: long rows in turn, then the short slices, longest
     // first, to the wave with the least work that has room
     std::vector<std::vector<std::pair<int64_t, int64_t>>> of_wave(waves);   // {first in order, rows}, -1 - w: long
@@ -143,11 +147,12 @@ bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const dou
         L.words[word] = half ? (L.words[word] & 0xffffu) | (position << 16) : (L.words[word] & 0xffff0000u) | position;
         if (!L.unit) L.vals[2 * word + half] = v;
     };
+    L.words.assign((size_t)L.word_rows * 64, pad);
+    if (!L.unit) L.vals.assign(2 * L.words.size(), 0.0);
+    size_t used = 0;                     // word rows; the spare ones stay behind the last
     auto grow = [&](size_t rows64) {
-        const size_t first = L.words.size() / 64;
-        L.words.resize(L.words.size() + rows64 * 64, pad);
-        if (!L.unit) L.vals.resize(2 * L.words.size(), 0.0);
-        return first;
+        used += rows64;
+        return used - rows64;
     };
     for (int w = 0; w < waves; ++w)
         for (int r = 0; r < L.rounds; ++r) {
@@ -194,7 +199,6 @@ bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const dou
                 }
             }
         }
-    grow(kResidentSpareRows);
     if (L.unit) {
         L.diag.assign(L.positions(), 0.0);
         for (int64_t i = 0; i < n; ++i)
@@ -202,7 +206,6 @@ bool build_resident_layout(const int32_t *row_ptr, const int32_t *col, const dou
                 if (col[p] == i) L.diag[pos[i]] = val[p];
     }
     *out = std::move(L);
-    return true;
 }
 
 }  // namespace vne

@@ -57,9 +57,19 @@ constexpr int64_t resident_max_word_rows(bool unit, bool fp64) {
     return (int64_t(1) << 32) / (unit ? 256 : fp64 ? 64 * 16 : 64 * 8);
 }
 
-// What the layout of build_resident_layout looks like, without it.
+// The rows as a shape goes by them: their entries in words, the rows by falling
+// length and how many of those are long.
+struct ResidentRows {
+    std::vector<int32_t> len, order;
+    int64_t n_long = 0;
+};
+
+// What the layout of build_resident_layout looks like, without it; lay_out
+// then makes it.
 bool resident_shape(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, int32_t waves,
-                    int32_t max_rounds, bool fp64, ResidentShape *out);
+                    int32_t max_rounds, bool fp64, ResidentShape *out, ResidentRows *rows);
+void lay_out(const int32_t *row_ptr, const int32_t *col, const double *val, int64_t n, const ResidentShape &shape,
+             const ResidentRows &rows, ResidentLayout *out);
 
 // us of one on-chip step of a workgroup with `cols` columns.
 double resident_step_us(const ResidentShape &s, int cols, bool fp64);

@@ -47,8 +47,12 @@ const ResidentShape *shape_of(vne_ctx *c, int32_t gid, int waves, bool fp64) {
     auto it = g->shapes.find(key);
     if (it == g->shapes.end()) {
         ResidentShape s;
-        if (!resident_shape(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves, slots(fp64), fp64, &s) ||
-            resident_lds(s.positions(), 1, fp64) > kResidentLds)
+        ResidentRows rows;
+        if (resident_shape(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves, slots(fp64), fp64, &s,
+                           &rows) &&
+            resident_lds(s.positions(), 1, fp64) <= kResidentLds)
+            g->shape_rows[key] = std::move(rows);
+        else
             s = ResidentShape();
         it = g->shapes.emplace(key, s).first;
     }
@@ -57,15 +61,20 @@ const ResidentShape *shape_of(vne_ctx *c, int32_t gid, int waves, bool fp64) {
 
 // The layout itself, for a run that takes it; null: does not fit, or no room.
 DevLayout *layout_of(vne_ctx *c, int32_t gid, int waves, bool fp64) {
-    if (!shape_of(c, gid, waves, fp64)) return nullptr;
+    const ResidentShape *s = shape_of(c, gid, waves, fp64);
+    if (!s) return nullptr;
     Graph *g = get_graph(c, gid);
     const auto key = std::make_pair(waves, (int)fp64);
     auto it = g->layouts.find(key);
     if (it != g->layouts.end()) return it->second.get();
     ResidentLayout h;
-    if (!build_resident_layout(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves, slots(fp64), &h,
-                               fp64))
+    auto rows = g->shape_rows.find(key);
+    if (rows != g->shape_rows.end())
+        lay_out(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, *s, rows->second, &h);
+    else if (!build_resident_layout(g->h_row_ptr.data(), g->h_col.data(), g->h_val.data(), g->n, waves, slots(fp64), &h,
+                                    fp64))
         return nullptr;
+    g->shape_rows.clear();
     auto d = std::make_unique<DevLayout>();
     d->waves = waves;
     d->rounds = h.rounds;
@@ -196,7 +205,9 @@ DevLayout *chip_choice(vne_ctx *c, GraphSet *set, const Plan *p, int *cols) {
     const ResidentShape *s = shape_of(c, set->ids[0], waves, fp64);
     if (!s) return nullptr;
     *cols = widest(*s, fp64, cap);
-    return slower(*s, *cols) ? nullptr : layout_of(c, set->ids[0], waves, fp64);
+    if (!slower(*s, *cols)) return layout_of(c, set->ids[0], waves, fp64);
+    get_graph(c, set->ids[0])->shape_rows.clear();
+    return nullptr;
 }
 
 DevLayout *chip_layout(vne_ctx *c, int32_t gid, int max_rounds) {
@@ -204,7 +215,9 @@ DevLayout *chip_layout(vne_ctx *c, int32_t gid, int max_rounds) {
     if (chip_mode() == 0 || c->budget != 0 || g->n > (int64_t)1024 * max_rounds) return nullptr;
     const int waves = (int)std::min<int64_t>(16, (g->n + 63) / 64);
     const ResidentShape *s = shape_of(c, gid, waves, true);
-    return s && s->rounds <= max_rounds ? layout_of(c, gid, waves, true) : nullptr;
+    if (s && s->rounds <= max_rounds) return layout_of(c, gid, waves, true);
+    get_graph(c, gid)->shape_rows.clear();
+    return nullptr;
 }
 
 vne_status run_chip(vne_ctx *c, GraphSet *set, Plan *p, const ProbeSpec &ps, bool desing, const DevLayout *L,
@@ -533,6 +546,7 @@ vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_
         large.clear();
         for (int q = 0; q < n_queries; ++q) {
             DevLayout *L = of[q] ? layout_of(c, ids[q], of[q]->waves, fp64) : nullptr;
+            get_graph(c, ids[q])->shape_rows.clear();
             if (!L) {
                 large.push_back(q);
                 continue;

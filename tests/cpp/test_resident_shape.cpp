@@ -31,8 +31,9 @@ int main() {
         for (int waves : {1, 4, 16}) {
             ResidentLayout L;
             ResidentShape s;
+            ResidentRows rows;
             const bool built = build_resident_layout(rp.data(), ci.data(), va.data(), n, waves, 19, &L, fp64);
-            if (built != resident_shape(rp.data(), ci.data(), va.data(), n, waves, 19, fp64, &s))
+            if (built != resident_shape(rp.data(), ci.data(), va.data(), n, waves, 19, fp64, &s, &rows))
                 return std::puts("FAIL one fits"), 1;
             if (!built) continue;
             int64_t most_rows = 0, most_tail = 0;
