@@ -137,19 +137,20 @@ bool long_rows_first(const Schedule &s, int64_t nnz, int m_pad, int mt, bool fp6
     //    narrow FP32 tiles, four or two rows a block, later: m = 10, 16
     //    columns 54 / 45), sooner where they are little more than a segment
     //    (ER of average degree 50, 64 columns 108 / 120), or where they are
-    //    many beside the step's time.
+    //    many beside the step's time; a few of them do not matter.
     const int lanes = mt / (fp64 ? 2 : mt % 3 == 0 ? 3 : 4);
     int i = 0;
     while (i + 1 < kLaneClasses && (2 << i) <= lanes) ++i;
     const bool narrow = !fp64 && lanes <= 8;
     const double share = (double)(s.long_entries + 4 * (int64_t)s.n_seg) / (double)(nnz + 4 * s.n_rows);
     const double mean = (double)s.long_entries / s.n_long;
-    if (share > (mean < 96.0 ? 0.02 : narrow ? 0.25 : 0.17)) return false;
+    if (s.n_long > 64 && share > (mean < 96.0 ? 0.02 : narrow ? 0.25 : 0.17)) return false;
     const double step_us = 15.0 + step_bytes_us(s.n_rows, nnz, m_pad, mt, fp64);      // 15: its launches
     const double round_us = lanes <= 2 ? 15.0 : fp64 ? (lanes <= 8 ? 9.0 : 5.6) : (lanes <= 8 ? 8.0 : 6.6);
     const double chain_us = round_us * s.front[i].most + 0.05 * s.most_segs;
-    return chain_us < std::max(round_us + 3.0, 0.45 * step_us) &&
-           m_pad / mt * s.front[i].idle < 16.0 * step_us;
+    // (hubs among many moderate long rows: the launch behind has more to add)
+    return chain_us < std::max(round_us + 3.0, (mean < 256.0 ? 0.6 : 0.45) * step_us) &&
+           m_pad / mt * s.front[i].idle < 24.0 * step_us;
 }
 
 Schedule build_schedule(const int32_t *row_ptr, int64_t n, int32_t seg_len, int64_t cost_per_block,
