@@ -626,18 +626,28 @@ vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_
         VNE_TRY(st);
     }
     HIP_TRY(c, hipEventRecord(c->side_events[0], c->stream));
-    for (size_t k = 0; k < b.classes.size(); ++k) {
-        const ChipBatch::Class &cl = b.classes[k];
-        hipStream_t s = c->side_streams[k];
-        HIP_TRY(c, hipStreamWaitEvent(s, c->side_events[0], 0));
-        HIP_TRY(c, launch_resident_many((const ResidentJob *)p->res_args.p,
-                                        (const int2 *)((const char *)p->res_args.p + cl.map_at), (int)cl.map.size(),
-                                        cl.waves, cl.kind, cl.lds, s));
-        HIP_TRY(c, hipEventRecord(c->side_events[1 + k], s));
-        // (at once: a class whose launch fails leaves none of the others
-        // running past the call's stream)
-        HIP_TRY(c, hipStreamWaitEvent(c->stream, c->side_events[1 + k], 0));
+    // (the classes that run are joined to the call's stream also where a later
+    // one fails; only after the last launch, since a wait on the null stream
+    // holds back what follows on the others: 64 graphs of 1000 to 10 000 rows, 8
+    // columns, 20 steps 1.50 ms with a wait between launches, 1.08 behind them)
+    hipError_t launched = hipSuccess;
+    size_t running = 0;
+    for (; running < b.classes.size() && launched == hipSuccess; ++running) {
+        const ChipBatch::Class &cl = b.classes[running];
+        hipStream_t s = c->side_streams[running];
+        launched = hipStreamWaitEvent(s, c->side_events[0], 0);
+        if (launched == hipSuccess)
+            launched = launch_resident_many((const ResidentJob *)p->res_args.p,
+                                            (const int2 *)((const char *)p->res_args.p + cl.map_at), (int)cl.map.size(),
+                                            cl.waves, cl.kind, cl.lds, s);
+        const hipError_t e = hipEventRecord(c->side_events[1 + running], s);
+        if (launched == hipSuccess) launched = e;
     }
+    for (size_t k = 0; k < running; ++k) {
+        const hipError_t e = hipStreamWaitEvent(c->stream, c->side_events[1 + k], 0);
+        if (launched == hipSuccess) launched = e;
+    }
+    HIP_TRY(c, launched);
     if (c->timing) {
         HIP_TRY(c, hipEventRecord(p->ev[1], c->stream));
         // one span: the bytes of either part's own steps, over the longer one's
