@@ -528,11 +528,14 @@ vne_status estimate_many(vne_ctx *c, const std::vector<int32_t> &ids, const vne_
             for (int q : large) stack(q);
             double work = 0.0;
             for (const Fit &f : fits) work += f.us * f.share * f.groups * k_steps[f.q];
+            // (only for a good eighth: the models are no better, and a first
+            // call pays for the larger stack and the trials of its tiles)
             double best = 0.0;
             for (size_t i = 0; i <= fits.size(); ++i) {
                 double us = sg == 0 ? 0.0 : sk * launched_us(sg == 1 ? kLaunchUs : kStackLaunchUs, sn, snnz, slong, sm, fp64);
                 if (i < fits.size()) us += std::max(fits[i].us * k_steps[fits[i].q], work / 256.0);
-                if (i == 0 || us < best) {
+                if (i == 0) best = 0.88 * us;
+                else if (us < best) {
                     best = us;
                     first = i;
                 }
