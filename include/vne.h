@@ -242,7 +242,8 @@ vne_status vne_entropy_estimate(vne_ctx *ctx, int32_t graph_id, const vne_probes
  * timing each admissible tile's whole captured step loop (VNE_AUTOTUNE=0
  * disables; VNE_AUTOTUNE_CACHE=<file> keeps the choices).  On a context with
  * no HBM budget, the graphs that fit in LDS (see vne_entropy_estimate) run
- * inside workgroups after the stacked steps of the others.  Errors: VNE_EINVAL for bad
+ * inside workgroups after the stacked steps of the others, except those for
+ * which the stack is faster by the rule on sizes.  Errors: VNE_EINVAL for bad
  * ids, sizes or mode bits; VNE_ENOMEM when the HBM budget is exceeded. */
 vne_status vne_entropy_estimate_batch(vne_ctx *ctx, int32_t n_queries, const int32_t *graph_ids,
                                       const vne_probes *probes, const int32_t *k_steps,

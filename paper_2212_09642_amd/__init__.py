@@ -438,7 +438,8 @@ class Context:
                              want_coeffs=want_coeffs, _entry="vne_entropy_estimate_noalloc")
 
     def estimate_batch(self, queries, mode, want_coeffs=False):
-        """Several queries in one stacked launch per step.  queries: list of
+        """Several queries at once (stacked launches per step; small graphs
+        inside workgroups).  queries: list of
         dicts with keys gid, kind, m, k and optionally seed, colors, dense
         (host arrays).  Returns one result dict per query."""
         nq = len(queries)

@@ -879,9 +879,7 @@ vne_status check_flags(vne_ctx *c, int32_t fl) {
     return VNE_OK;
 }
 
-// Results of every graph of the plan: one device-to-host copy per array,
-// then scattered into out[q] (m[q] columns, k[q] steps).  Also reads the
-// flag word of the plan (and of extra, if given) and synchronises.
+// At least `bytes` of pinned staging memory for the plan's results.
 vne_status stage_room(vne_ctx *c, Plan *p, size_t bytes) {
     if (p->h_stage_bytes >= bytes) return VNE_OK;
     if (p->h_stage) {
@@ -940,6 +938,9 @@ vne_status fetch_results(vne_ctx *c, Plan *p, ResultPart *parts, int n, int comb
     return VNE_OK;
 }
 
+// Results of every graph of the plan, fetched by one launch (or by copies, see
+// kCollectBytes), then scattered into out[q] (m[q] columns, k[q] steps).  Also
+// reads the flag word of the plan (and of extra, if given).
 vne_status copy_out(vne_ctx *c, Plan *p, const int32_t *m, const int32_t *k, vne_result *out, Plan *extra,
                     int combine_kind) {
     const int G = p->G;
